@@ -1,30 +1,30 @@
 // Gating (§2.1): gate logits, top-k selection and renormalised gate weights.
 //
-// One wave per token at a time. In weight mode each lane accumulates its
-// stride of the hidden dimension in float64 for 8 experts at a time
-// (bf16*bf16 products are exact in float64), a DPP reduction gives every
-// lane the full sums, and the float64 sum is rounded once to float32.
-// When the gate matrix fits (E*d*2 <= 96 KB) a block of 16 waves (16
-// tokens) stages it in LDS once, so the matrix is read from memory once per
-// 16 tokens instead of once per token; up to E*d*4 = 128 KB it is staged
-// widened to float32, which takes the unpacking out of the dot product (the
-// loop is bound by the vector ALU). Top-k runs as k rounds of a wave
-// arg-max over the float32 logits (larger first, ties to the lower expert
-// id), the cross-lane step in DPP row operations and lane reads; lane j
-// keeps the j-th winner, the k exponentials are formed in parallel and
-// summed in rank order.
+// In weight mode every logit that is returned, compared or turned into a gate
+// weight is a float64 sum of the exact bf16 x bf16 products, rounded once to
+// float32. Three kernels form them, chosen by launch_gate_topk from the sizes:
+//   token   one token per block, the vector unit's float64 FMA (few tokens);
+//   dense   all logits by float64 MFMA into memory, then the top-k over
+//           them (logits wanted, or memory for them at hand);
+//   screen  bf16 MFMA sums with an error bound tell which experts can be
+//           among the k largest; only those get a float64 logit.
+// The float64 sums of the first and the last run in the same order; dense
+// has another, so a logit that lies within float64 rounding of a float32
+// midpoint may differ between them.
+//
+// Top-k runs as k rounds of a wave arg-max over the float32 logits (larger
+// first, ties to the lower expert id), the cross-lane step in DPP row
+// operations and lane reads; lane j keeps the j-th winner, the k
+// exponentials are formed in parallel and summed in rank order.
+#include <type_traits>
+
 #include "tg_device.h"
 #include "tg_launch.h"
 
 namespace tg {
 namespace {
 
-constexpr int kWaves = 4;          // waves per block (unstaged kernels)
-constexpr int kStagedWaves = 16;   // waves (= tokens) per block when the gate matrix is staged
-constexpr int kStageElems = 48 * 1024;  // 96 KB of bf16
-constexpr int kStageElemsF32 = 32 * 1024;  // 128 KB of float32
-constexpr int kStageBytes = 128 * 1024;
-constexpr int kStagedMaxE = kStageElems / 256;  // staged only when E * d fits, d >= 256
+constexpr int kWaves = 4;  // waves per block of logits_topk_kernel
 
 __device__ __forceinline__ bool better(float v, int id, float bv, int bid) {
   return v > bv || (v == bv && id < bid);
@@ -49,6 +49,39 @@ __device__ __forceinline__ void row_best(float& bv, int& bid) {
   TG_DPP_STEP(0x141);  // row_half_mirror
   TG_DPP_STEP(0x140);  // row_mirror
 #undef TG_DPP_STEP
+}
+
+// The same over the wave: the four rows are compared with lane reads.
+__device__ __forceinline__ void wave_best(float& bv, int& bid) {
+  row_best(bv, bid);
+  float gv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bv), 0));
+  int gid = __builtin_amdgcn_readlane(bid, 0);
+#pragma unroll
+  for (int r = 1; r < 4; ++r) {
+    const float rv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bv), 16 * r));
+    const int rid = __builtin_amdgcn_readlane(bid, 16 * r);
+    if (better(rv, rid, gv, gid)) {
+      gv = rv;
+      gid = rid;
+    }
+  }
+  bv = gv;
+  bid = gid;
+}
+
+// Lane j < k holds the token's j-th choice: its id and its weight
+// exp(l_j - l_0) / sum_{j'<k} exp(l_j' - l_0), the sum in rank order.
+__device__ __forceinline__ void store_topk(float my_v, int my_id, int k, int t,
+                                           int32_t* __restrict__ ids, float* __restrict__ w) {
+  const int lane = lane_id();
+  const float v0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), 0));
+  const float ex = (lane < k) ? expf(my_v - v0) : 0.0f;
+  float z = 0.0f;
+  for (int j = 0; j < k; ++j) z += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ex), j));
+  if (lane < k) {
+    ids[(size_t)t * k + lane] = my_id;
+    w[(size_t)t * k + lane] = ex / z;
+  }
 }
 
 // Top-k over the logits held in `lg` (LDS, E <= 64 * NQ floats) by one
@@ -79,33 +112,31 @@ __device__ void wave_topk(const float* lg, int E, int k, int t, int32_t* __restr
         bid = e;
       }
     }
-    row_best(bv, bid);
-    float gv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bv), 0));
-    int gid = __builtin_amdgcn_readlane(bid, 0);
-#pragma unroll
-    for (int r = 1; r < 4; ++r) {
-      const float rv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bv), 16 * r));
-      const int rid = __builtin_amdgcn_readlane(bid, 16 * r);
-      if (better(rv, rid, gv, gid)) {
-        gv = rv;
-        gid = rid;
-      }
-    }
-    if ((gid & (kWave - 1)) == lane) taken |= 1u << (gid / kWave);
+    wave_best(bv, bid);
+    if ((bid & (kWave - 1)) == lane) taken |= 1u << (bid / kWave);
     if (lane == j) {
-      my_v = gv;
-      my_id = gid;
+      my_v = bv;
+      my_id = bid;
     }
   }
-  // w_j = exp(l_j - l_0) / sum_{j'<k} exp(l_j' - l_0), the sum in rank order.
-  const float v0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), 0));
-  const float ex = (lane < k) ? expf(my_v - v0) : 0.0f;
-  float z = 0.0f;
-  for (int j = 0; j < k; ++j) z += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ex), j));
-  if (lane < k) {
-    ids[(size_t)t * k + lane] = my_id;
-    w[(size_t)t * k + lane] = ex / z;
+  store_topk(my_v, my_id, k, t, ids, w);
+}
+
+// Top-k over n <= 64 candidates, lane l < n holding candidate l (n >= k, ids
+// distinct): a lane's rank is the number of candidates that beat its own.
+__device__ void wave_topk_lanes(float v, int id, int n, int k, int t, int32_t* __restrict__ ids,
+                                float* __restrict__ w) {
+  const int lane = lane_id();
+  int rank = 0;
+  for (int i = 0; i < n; ++i) {
+    const float ov = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
+    const int oid = __builtin_amdgcn_readlane(id, i);
+    rank += better(ov, oid, v, id) ? 1 : 0;
   }
+  const int to = 4 * (lane < n ? rank : lane);
+  const float my_v = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(v)));
+  const int my_id = __builtin_amdgcn_ds_permute(to, id);
+  store_topk(my_v, my_id, k, t, ids, w);
 }
 
 // wave_topk for the smallest NQ that covers E.
@@ -145,131 +176,407 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return total;
 }
 
-// float64 logits of token t for experts e0..e0+7 against a gate matrix
-// (global or LDS), written to lg by lane 0 after a wave reduction.
-template <typename WgPtr>
-__device__ __forceinline__ void logits8(const uint4* __restrict__ xr, WgPtr wg, int d, int E,
-                                        int e0, float* lg) {
-  const int lane = lane_id();
+// float64 logits of one token for the NC experts e[0..NC-1] (wave-uniform).
+// Lane l sums 8-element chunks l, l + 64, ... of the row, then the lanes are
+// added. The vector unit bounds it: per product and wave an unpack, a
+// widening (8 cycles, measured) and an FMA, 16 cycles; the next chunk's loads
+// are in flight meanwhile.
+template <int NC>
+__device__ __forceinline__ void logits_of(const uint4* __restrict__ xr,
+                                          const uint16_t* __restrict__ wg, int d, const int* e,
+                                          float* out) {
   const int nchunk = d / 8;
-  double acc[8];
+  double acc[NC];
+  uint4 xn, wn[NC];
+  auto load = [&](int c) {
+    xn = xr[c];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0.0;
-  for (int c = lane; c < nchunk; c += kWave) {
-    const uint4 xv = xr[c];
-    const uint32_t xs[4] = {xv.x, xv.y, xv.z, xv.w};
-    double xd[8];
+    for (int q = 0; q < NC; ++q) wn[q] = reinterpret_cast<const uint4*>(wg + (size_t)e[q] * d)[c];
+  };
+#pragma unroll
+  for (int q = 0; q < NC; ++q) acc[q] = 0.0;
+  load(min(lane_id(), nchunk - 1));
+  for (int c = lane_id(); c < nchunk; c += kWave) {
+    const uint32_t xs[4] = {xn.x, xn.y, xn.z, xn.w};
+    uint4 wv[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) wv[q] = wn[q];
+    load(min(c + kWave, nchunk - 1));  // one chunk ahead
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      xd[2 * i] = (double)__uint_as_float(xs[i] << 16);
-      xd[2 * i + 1] = (double)__uint_as_float(xs[i] & 0xffff0000u);
+      const double x0 = (double)__uint_as_float(xs[i] << 16);
+      const double x1 = (double)__uint_as_float(xs[i] & 0xffff0000u);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const uint32_t ws[4] = {wv[q].x, wv[q].y, wv[q].z, wv[q].w};
+        acc[q] = fma(x0, (double)__uint_as_float(ws[i] << 16), acc[q]);
+        acc[q] = fma(x1, (double)__uint_as_float(ws[i] & 0xffff0000u), acc[q]);
+      }
     }
+  }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = e0 + q;
-      if (e < E) {
-        const uint4 wv = reinterpret_cast<const uint4*>(wg + (size_t)e * d)[c];
-        const uint32_t ws[4] = {wv.x, wv.y, wv.z, wv.w};
+  for (int q = 0; q < NC; ++q) out[q] = (float)wave_sum_f64(acc[q]);
+}
+
+// logits_of for the first 8, 4, 2 or 1 of n experts: id(j) gives the j-th,
+// out(j, logit) takes its logit on every lane. Returns how many.
+template <typename Id, typename Out>
+__device__ __forceinline__ int run_of_logits(const uint4* __restrict__ xr,
+                                             const uint16_t* __restrict__ wg, int d, int n, Id id,
+                                             Out out) {
+  auto take = [&](auto nc) {
+    constexpr int NC = decltype(nc)::value;
+    int e[NC];
+    float v[NC];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[q] = fma(xd[2 * i], (double)__uint_as_float(ws[i] << 16), acc[q]);
-          acc[q] = fma(xd[2 * i + 1], (double)__uint_as_float(ws[i] & 0xffff0000u), acc[q]);
+    for (int j = 0; j < NC; ++j) e[j] = id(j);
+    logits_of<NC>(xr, wg, d, e, v);
+#pragma unroll
+    for (int j = 0; j < NC; ++j) out(j, v[j]);
+    return NC;
+  };
+  if (n >= 8) return take(std::integral_constant<int, 8>{});
+  if (n >= 4) return take(std::integral_constant<int, 4>{});
+  if (n >= 2) return take(std::integral_constant<int, 2>{});
+  return take(std::integral_constant<int, 1>{});
+}
+
+// Weight mode for many experts: a screen on the matrix cores, then float64
+// logits only for the experts that can be among the k largest.
+//
+// Screen: 16 waves form s~[t,e], the float32 dot products of TT token rows
+// with every gate row, by v_mfma_f32_16x16x32_bf16, and beside them
+// a[t,e] = sum_i |x_i w_i| from the same fragments with the sign bits
+// cleared. bf16 products are exact in float32, so |s~ - s| comes from the
+// additions alone: an accumulator takes at most 256 products before it is
+// added to the wave's float32 total and cleared, and each of those
+// additions, however the unit orders or truncates them, loses at most
+// 2^-23 of the running magnitude, which a bounds. With nadd additions on any
+// product's way, |s~ - s| <= nadd * 2^-23 * a; the host passes twice that,
+// and a term for products below the smallest float32 (`tiny`). (Denormal
+// bf16 inputs and float32 results are kept by this instruction: checked on
+// an MI355X, where the largest error found over adversarial operands was
+// 2.5 * 2^-23 * a for an instruction's 32 products.) A bound that is not
+// finite keeps its expert.
+//
+// Selection: tau, the k-th largest s~ - B, is at most the k-th largest exact
+// logit, so an expert with s~ + B < tau cannot be chosen, nor tie. The
+// others (k and, for independent inputs, less than one more) get their
+// float64 logits, one wave per token, and the top-k runs over those: ids and
+// weights have the bits that all E float64 logits would give.
+//
+// Both operands go global -> LDS with buffer loads that write LDS directly,
+// 128 bytes of a row at a time, through a ring of NB stage buffers; 16-byte
+// chunks sit XOR-swizzled in their row against bank conflicts. A stage holds
+// 256 gate-matrix rows of 64 elements: for
+// P = 1 rows of 256 experts, for P > 1 the rows of 256 / P experts at P
+// consecutive 64-element pieces of the hidden dimension. A wave multiplies
+// two tiles of 16 experts by one 32-deep half of their stage, so that a token
+// fragment read from LDS serves two products (with one tile and both halves
+// per wave the LDS reads, 64 KB a stage, set the pace); the 2 P parts' sums
+// are added at the end.
+constexpr int kScreenWaves = 16;  // waves, and tokens, per block
+
+template <int P>
+struct ScreenShape {
+  static constexpr int TT = 16;                // tokens per block
+  static constexpr int GE = 256 / P;           // experts at once
+  static constexpr int NB = P == 4 ? 3 : 4;    // stage buffers
+  static constexpr int W_ST = 256 * 64;        // elements per stage
+  static constexpr int X_ST = P * TT * 64;
+  static constexpr int LDS = NB * (W_ST + X_ST) * 2;
+  static_assert(LDS <= 160 * 1024 && 2 * P * TT * GE * 8 <= LDS, "the sums take the ring's place");
+};
+
+typedef uint32_t u32x4g __attribute__((ext_vector_type(4)));
+
+// XOR swizzle of the eight 16-byte chunks of a staged row.
+__device__ __forceinline__ int screen_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+
+__device__ __forceinline__ float wave_max_f32(float v) {
+#define TG_DPP_FMAX(ctrl)                                                               \
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xF, 0xF, \
+                                                          false)))
+  TG_DPP_FMAX(0xB1);
+  TG_DPP_FMAX(0x4E);
+  TG_DPP_FMAX(0x141);
+  TG_DPP_FMAX(0x140);
+#undef TG_DPP_FMAX
+  float m = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
+#pragma unroll
+  for (int r = 1; r < 4; ++r)
+    m = fmaxf(m, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16 * r)));
+  return m;
+}
+
+// Top-k of one token by one wave: lane l holds the bounds lo and hi of the
+// experts l, l + 64, ... `scratch`: LDS of the wave's own, 6 E bytes.
+template <int NQ>
+__device__ __forceinline__ void screened_topk(const float* lo, const float* hi, char* scratch,
+                                              const uint4* __restrict__ xr,
+                                              const uint16_t* __restrict__ wg, int d, int E, int k,
+                                              int t, int32_t* __restrict__ ids,
+                                              float* __restrict__ w) {
+  const int lane = lane_id();
+  // tau: the k-th largest of the lanes' largest lower bounds, or lower where
+  // lanes are equal. k experts reach it, so it is at most the k-th largest of
+  // all lower bounds (two of the k largest in one lane cost a candidate).
+  float best = lo[0];
+#pragma unroll
+  for (int q = 1; q < NQ; ++q) best = fmaxf(best, lo[q]);
+  float tau = 0.0f;
+  for (int j = 0; j < k; ++j) {
+    tau = wave_max_f32(best);
+    best = best == tau ? -__builtin_inff() : best;
+  }
+  // The candidates in expert order, as a list in LDS.
+  float* const lg = reinterpret_cast<float*>(scratch);
+  uint16_t* const list = reinterpret_cast<uint16_t*>(lg + E);
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  int n = 0;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int e = lane + q * kWave;
+    const bool on = e < E && !(hi[q] < tau);
+    const uint64_t m = __ballot(on);
+    if (on) list[n + __builtin_popcountll(m & lt)] = (uint16_t)e;
+    if (e < E) lg[e] = -__builtin_inff();
+    n += __builtin_popcountll(m);
+  }
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  float my_v = -__builtin_inff();
+  for (int i = 0; i < n;) {
+    i += run_of_logits(xr, wg, d, n - i,
+                       [&](int j) { return __builtin_amdgcn_readfirstlane((int)list[i + j]); },
+                       [&](int j, float v) {
+                         if (n <= kWave) my_v = (lane == i + j) ? v : my_v;
+                         else if (lane == 0) lg[list[i + j]] = v;
+                       });
+  }
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  if (n > kWave) {
+    wave_topk<NQ>(lg, E, k, t, ids, w);
+  } else {  // lane l holds candidate l
+    const int id = lane < n ? (int)list[lane] : 0x7fffffff;
+    wave_topk_lanes(my_v, id, n, k, t, ids, w);
+  }
+}
+
+template <int P, int NG>
+__global__ __launch_bounds__(64 * kScreenWaves) void gate_screen_topk_kernel(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int T, int d, int E, int k,
+    float bound, float tiny, int32_t* __restrict__ ids, float* __restrict__ w) {
+  using Sh = ScreenShape<P>;
+  constexpr int TT = Sh::TT, GE = Sh::GE, NB = Sh::NB, W_ST = Sh::W_ST, X_ST = Sh::X_ST;
+  constexpr int kOut = (int)0x80000000u;  // an offset past any resource: reads zeros
+  constexpr int XI = X_ST / 512;          // x load instructions per stage (512 elements each)
+  __shared__ __attribute__((aligned(16))) uint16_t smem[Sh::LDS / 2];
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int t0 = blockIdx.x * TT;
+  const int nstage = (d + 64 * P - 1) / (64 * P);
+  lds_u16* const smem3 = (lds_u16*)smem;
+
+  // Load instruction i of a stage fills 8 rows of 128 bytes; lane l writes
+  // chunk position l % 8 of row l / 8 and fetches the chunk that the swizzle
+  // puts there. Wave w loads rows 16 w .. 16 w + 15 of the gate matrix's
+  // stage, the first XI waves 8 rows of x each. Experts past the last read
+  // zeros, as do tokens past the last and pieces past d.
+  const __amdgpu_buffer_rsrc_t x_rsrc =
+      make_rsrc(x + (size_t)t0 * d, (uint32_t)min(TT, T - t0) * d * 2);
+  const int wp = wave * 16 / GE;  // the wave's piece of the hidden dimension
+  int w_off[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = wave * 16 + i * 8 + lane / 8;
+    w_off[i] = ((r % GE) * d + wp * 64 + ((lane % 8) ^ screen_swz(r)) * 8) * 2;
+  }
+  const int xp = wave / 2;  // piece and rows of the wave's x load (wave < XI)
+  const int xr = (wave % 2) * 8 + lane / 8;
+  const int x_off = (xr * d + xp * 64 + ((lane % 8) ^ screen_swz(xr)) * 8) * 2;
+  __amdgpu_buffer_rsrc_t w_rsrc;
+  auto issue = [&](int st, int buf) {
+    const int k0 = min(st, nstage - 1) * 64 * P;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      load_lds16(w_rsrc, smem3 + buf * W_ST + (wave * 16 + i * 8) * 64,
+                 k0 + wp * 64 < d ? w_off[i] : kOut, k0 * 2);
+    if (wave < XI)
+      load_lds16(x_rsrc, smem3 + NB * W_ST + buf * X_ST + wave * 512,
+                 k0 + xp * 64 < d ? x_off : kOut, k0 * 2);
+  };
+  // The wave multiplies rows 32 (w / 2) .. + 31 of a stage by its half w % 2.
+  // Fragments: row l % 16 of a tile (or of x), chunk 4 half + l / 16.
+  const int half = wave & 1, fr = (wave >> 1) * 32 + (lane & 15), fp = (wave >> 1) * 32 / GE;
+  const int fchunk = 4 * half + lane / 16;
+  const int woff[2] = {fr * 64 + ((fchunk ^ screen_swz(fr)) << 3),
+                       (fr + 16) * 64 + ((fchunk ^ screen_swz(fr + 16)) << 3)};
+  const int xoff = NB * W_ST + (fp * TT + (lane & 15)) * 64 + ((fchunk ^ screen_swz(lane & 15)) << 3);
+
+  // Lane l: bounds of experts l, l + 64, ... for the wave's token, group by group.
+  constexpr int GQ = GE / kWave, NQ = NG * GQ;
+  float lo[NQ], hi[NQ];
+  const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int ne = min(max(E - g * GE, 0), GE);  // experts of this group
+    w_rsrc = make_rsrc(wg + (size_t)g * GE * d, (uint32_t)ne * d * 2);
+    f32x4 tot[2] = {zero, zero}, tota[2] = {zero, zero}, acc[2] = {zero, zero},
+          acca[2] = {zero, zero};
+#pragma unroll
+    for (int j = 0; j < NB - 1; ++j) issue(j, j);
+    for (int st = 0; st < nstage; ++st) {
+      // Stage st has landed for every wave, and every wave is done with stage
+      // st - 1, whose buffer takes stage st + NB - 1.
+      if (wave < XI) TG_WAIT_VM((NB - 2) * 3);
+      else TG_WAIT_VM((NB - 2) * 2);
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+      block_barrier();
+      issue(st + NB - 1, (st + NB - 1) % NB);
+      const u32x4g xf = *reinterpret_cast<const u32x4g*>(smem + (st % NB) * X_ST + xoff);
+      const u32x4g xa = xf & 0x7fff7fffu;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const u32x4g wf = *reinterpret_cast<const u32x4g*>(smem + (st % NB) * W_ST + woff[b]);
+        const u32x4g wa = wf & 0x7fff7fffu;
+        acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, xf), __builtin_bit_cast(bf16x8, wf), acc[b], 0, 0, 0);
+        acca[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, xa), __builtin_bit_cast(bf16x8, wa), acca[b], 0, 0, 0);
+      }
+      if ((st & 7) == 7 || st == nstage - 1) {  // 256 products
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          tot[b] += acc[b];
+          tota[b] += acca[b];
+          acc[b] = acca[b] = zero;
         }
       }
     }
-  }
+    TG_WAIT_VM(0);
+    __syncthreads();  // no load may land in the ring any more
+    // Register r of lane l: token 4 (l / 16) + r, expert l % 16 of the tile.
+    float2* const part = reinterpret_cast<float2*>(smem);  // [2 P][TT][GE]
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const double sum = wave_sum_f64(acc[q]);
-    if (lane == 0 && e0 + q < E) lg[e0 + q] = (float)sum;
-  }
-}
-
-// The same against a gate matrix staged in LDS as float32 (two float4 per
-// chunk of 8), which saves the unpacking of every weight; the products and
-// their order are those of logits8.
-__device__ __forceinline__ void logits8_f32(const uint4* __restrict__ xr, const float* wg, int d,
-                                            int E, int e0, float* lg) {
-  const int lane = lane_id();
-  const int nchunk = d / 8;
-  double acc[8];
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0.0;
-  for (int c = lane; c < nchunk; c += kWave) {
-    const uint4 xv = xr[c];
-    const uint32_t xs[4] = {xv.x, xv.y, xv.z, xv.w};
-    double xd[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      xd[2 * i] = (double)__uint_as_float(xs[i] << 16);
-      xd[2 * i + 1] = (double)__uint_as_float(xs[i] & 0xffff0000u);
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int e = e0 + q;
-      if (e < E) {
-        const float4* wr = reinterpret_cast<const float4*>(wg + (size_t)e * d) + 2 * c;
-        const float4 w0 = wr[0], w1 = wr[1];
-        const float wf[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[q] = fma(xd[i], (double)wf[i], acc[q]);
-      }
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const double sum = wave_sum_f64(acc[q]);
-    if (lane == 0 && e0 + q < E) lg[e0 + q] = (float)sum;
-  }
-}
-
-// Weight mode, one token per wave. STAGE 0: 4 waves read the gate matrix
-// from global memory; otherwise a block of 16 waves first copies it to LDS,
-// as bf16 (STAGE 1) or, when it fits in 128 KB that way, widened to float32
-// (STAGE 2).
-template <int STAGE>
-__global__ __launch_bounds__(STAGE ? 64 * kStagedWaves : 64 * kWaves) void gate_weights_topk_kernel(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int T, int d, int E, int k,
-    float* __restrict__ logits_out, int32_t* __restrict__ ids, float* __restrict__ w) {
-  constexpr int NW = STAGE ? kStagedWaves : kWaves;
-  constexpr int LG = STAGE ? kStagedMaxE : 1024;
-  __shared__ __attribute__((aligned(16))) uint32_t wg_s[STAGE ? kStageBytes / 4 : 4];
-  __shared__ float lg_s[NW][LG];
-  const int wave = threadIdx.x / kWave;
-  const int lane = lane_id();
-  float* lg = lg_s[wave];
-  if (STAGE) {
-    const int n16 = E * d / 8;
-    for (int i = threadIdx.x; i < n16; i += 64 * NW) {
-      const uint4 v = reinterpret_cast<const uint4*>(wg)[i];
-      if (STAGE == 1) {
-        reinterpret_cast<uint4*>(wg_s)[i] = v;
-      } else {
-        const uint32_t m = 0xffff0000u;
-        reinterpret_cast<uint4*>(wg_s)[2 * i] = make_uint4(v.x << 16, v.x & m, v.y << 16, v.y & m);
-        reinterpret_cast<uint4*>(wg_s)[2 * i + 1] =
-            make_uint4(v.z << 16, v.z & m, v.w << 16, v.w & m);
-      }
-    }
+      for (int r = 0; r < 4; ++r)
+        part[((2 * fp + half) * TT + 4 * (lane / 16) + r) * GE + (fr + 16 * b) % GE] =
+            make_float2(tot[b][r], tota[b][r]);
     __syncthreads();
+#pragma unroll
+    for (int q = 0; q < GQ; ++q) {
+      const int e = lane + q * kWave;
+      float s = 0.0f, a = 0.0f;
+#pragma unroll
+      for (int p = 0; p < 2 * P; ++p) {
+        const float2 v = part[(p * TT + wave) * GE + e];
+        s += v.x;
+        a += v.y;
+      }
+      const float bd = fmaf(a, bound, tiny);
+      // Not finite: nothing is known of this logit.
+      const bool known = bd < __builtin_inff();
+      lo[g * GQ + q] = e < ne && known ? s - bd : -__builtin_inff();
+      hi[g * GQ + q] = e < ne ? (known ? s + bd : __builtin_inff()) : -__builtin_inff();
+    }
+    __syncthreads();  // the sums have been read: the ring and the scratch take their place
   }
-  const int t = blockIdx.x * NW + wave;
-  if (t < T) {
-    const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)t * d);
-    for (int e0 = 0; e0 < E; e0 += 8) {
-      if (STAGE == 2)
-        logits8_f32(xr, reinterpret_cast<const float*>(wg_s), d, E, e0, lg);
-      else if (STAGE == 1)
-        logits8(xr, reinterpret_cast<const uint16_t*>(wg_s), d, E, e0, lg);
-      else
-        logits8(xr, wg, d, E, e0, lg);
+  const int t = t0 + wave;  // one token per wave
+  if (t < T)
+    screened_topk<NQ>(lo, hi, reinterpret_cast<char*>(smem) + (size_t)wave * 6 * NG * GE,
+                      reinterpret_cast<const uint4*>(x + (size_t)t * d), wg, d, E, k, t, ids, w);
+}
+
+// Weight mode, few tokens: one token per block of NW waves, each taking an
+// equal run of experts, up to eight at a time, straight from L2. (One token
+// per wave would leave most of the chip idle.)
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void gate_token_topk_kernel(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int d, int E, int k,
+    float* __restrict__ logits_out, int32_t* __restrict__ ids, float* __restrict__ w) {
+  __shared__ float lg[1024];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int t = blockIdx.x;
+  const uint4* const xr = reinterpret_cast<const uint4*>(x + (size_t)t * d);
+  const int per = (E + NW - 1) / NW, end = min(E, (wave + 1) * per);
+  for (int e0 = wave * per; e0 < end;) {
+    e0 += run_of_logits(xr, wg, d, end - e0, [&](int j) { return e0 + j; },
+                        [&](int j, float v) {
+                          if (lane_id() == 0) {
+                            lg[e0 + j] = v;
+                            if (logits_out) logits_out[(size_t)t * E + e0 + j] = v;
+                          }
+                        });
+  }
+  __syncthreads();
+  if (wave == 0) wave_topk_any(lg, E, k, t, ids, w);
+}
+
+// All logits [T, E] in float64 on the matrix cores (v_mfma_f64_16x16x4: the
+// rate of the vector unit's float64 FMA, but the operands are widened once
+// per 16 tokens or experts instead of once per product, beside it). A block
+// of 16 waves forms 16 tokens x 16 experts, each wave over every 16th
+// 32-element piece of the hidden dimension (the split keeps few tokens from
+// being one long chain; wider tiles with fewer waves measured 5 % faster at
+// 4096 tokens of 256 experts and half as fast at 128); the parts are added
+// in LDS in a fixed order and the float64 sum is rounded once. Lane l holds
+// row l % 16, elements 8 (l / 16) .. + 7 of a piece; step j multiplies
+// element j of every lane. 4096 x 256 x 7168: 282 us, 53 TFLOP/s of float64.
+// TOPK (E <= 16): the block holds all logits of its tokens and finishes them,
+// one wave each; logits may then be null.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kDenseWaves = 16;
+template <bool TOPK>
+__global__ __launch_bounds__(64 * kDenseWaves) void gate_logits_f64_kernel(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int T, int d, int E, int k,
+    float* __restrict__ logits, int32_t* __restrict__ ids, float* __restrict__ w) {
+  __shared__ float lg[TOPK ? 16 : 1][16];
+  __shared__ f64x4 part[kDenseWaves - 1][kWave];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lane = lane_id();
+  const int t0 = blockIdx.x * 16, e0 = blockIdx.y * 16;
+  // Rows past the last token or expert repeat it; they are not stored.
+  const uint16_t* const xr = x + (size_t)min(t0 + (lane & 15), T - 1) * d + 8 * (lane / 16);
+  const uint16_t* const wr = wg + (size_t)min(e0 + (lane & 15), E - 1) * d + 8 * (lane / 16);
+  const int np = d / 32;
+  auto widen = [](const uint4& v, int j) {
+    const uint32_t u = (j >> 1) == 0 ? v.x : (j >> 1) == 1 ? v.y : (j >> 1) == 2 ? v.z : v.w;
+    return (double)__uint_as_float((j & 1) ? u & 0xffff0000u : u << 16);
+  };
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  uint4 xn, wn;
+  auto load = [&](int p) {
+    p = min(p, np - 1);
+    xn = *reinterpret_cast<const uint4*>(xr + p * 32);
+    wn = *reinterpret_cast<const uint4*>(wr + p * 32);
+  };
+  load(wave);
+  for (int p = wave; p < np; p += kDenseWaves) {
+    const uint4 xv = xn, wv = wn;
+    load(p + kDenseWaves);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(widen(xv, j), widen(wv, j), acc, 0, 0, 0);
+  }
+  if (wave > 0) part[wave - 1][lane] = acc;
+  __syncthreads();
+  if (wave == 0) {
+    for (int q = 0; q < kDenseWaves - 1; ++q) acc += part[q][lane];
+    // Register r of lane l: token 4 r + l / 16, expert l % 16.
+    const int e = e0 + (lane & 15);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int t = t0 + 4 * r + lane / 16;
+      if (TOPK) lg[4 * r + lane / 16][lane & 15] = (float)acc[r];
+      if (t < T && e < E && (!TOPK || logits)) logits[(size_t)t * E + e] = (float)acc[r];
     }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    if (logits_out) {
-      for (int e = lane; e < E; e += kWave) logits_out[(size_t)t * E + e] = lg[e];
-    }
-    wave_topk_any(lg, E, k, t, ids, w);
+  }
+  if (TOPK) {
+    __syncthreads();
+    if (t0 + wave < T) wave_topk<1>(lg[wave], E, k, t0 + wave, ids, w);
   }
 }
 
@@ -368,36 +675,115 @@ __global__ __launch_bounds__(256) void logits_topk_rows_kernel(const float* __re
   }
 }
 
+// Additions on the way of any product of the screen: 256 within an
+// accumulator, one per chunk, and the parts' sum; doubled.
+template <int P, int NG>
+void launch_screen(const uint16_t* x, const uint16_t* wg, int T, int d, int E, int k, int32_t* ids,
+                   float* w, hipStream_t stream) {
+  constexpr int TT = ScreenShape<P>::TT;
+  const double nadd = 256.0 + (d / 64 + 7) / 8 + 2 * P;
+  const float bound = (float)(2.0 * nadd * 0x1p-23), tiny = (float)(d * 0x1p-126);
+  hipLaunchKernelGGL((gate_screen_topk_kernel<P, NG>), dim3((T + TT - 1) / TT),
+                     dim3(64 * kScreenWaves), 0, stream, x, wg, T, d, E, k, bound,
+                     tiny, ids, w);
+}
+
+void launch_logits_topk(const float* logits, int T, int E, int k, int32_t* ids, float* w,
+                        hipStream_t stream) {
+  if (E <= 256 && k <= 16 && T >= 4096) {
+    const int per_block = 4 * kRowTokens;  // 4 waves of 4 tokens
+    const dim3 grid((T + per_block - 1) / per_block);
+    if (E <= 64)
+      hipLaunchKernelGGL(logits_topk_rows_kernel<4>, grid, dim3(256), 0, stream, logits, T, E, k,
+                         ids, w);
+    else if (E <= 128)
+      hipLaunchKernelGGL(logits_topk_rows_kernel<8>, grid, dim3(256), 0, stream, logits, T, E, k,
+                         ids, w);
+    else
+      hipLaunchKernelGGL(logits_topk_rows_kernel<16>, grid, dim3(256), 0, stream, logits, T, E, k,
+                         ids, w);
+  } else {
+    hipLaunchKernelGGL(logits_topk_kernel, dim3((T + kWaves - 1) / kWaves), dim3(256), 0, stream,
+                       logits, T, E, k, ids, w);
+  }
+}
+
+// Which kernel forms the logits in weight mode. `stored`: there is memory for
+// all T x E logits (the caller wants them, or has scratch to lend). Measured,
+// us, back-to-back calls of tg_gate_topk, whose host side alone takes about
+// 8 us (dense counts its second launch, the top-k, from E = 17 on; `before`:
+// one token per wave, the gate matrix in LDS where it fits, else from L2):
+//   d, E, k       T =            1    128    512   1024   2048   4096
+//   7168, 256, 8  token         58     58      -      -      -      -
+//                 dense         27     30     47     79    146    282
+//                 screen        71     96    100    101    101    105
+//                 before      1073   1177   1184   1212   1185   1334
+//   4096, 64, 6   token         12     13      -      -      -      -
+//                 dense         16     17     18     19     28     46
+//                 screen        19     30     31     31     32     34
+//                 before        94    116    111    178    176    187
+//   7168, 16, 8   token          -      -     18     32      -      -
+//                 dense          -      -     27     27     27     27
+//                 before         -      -     51     79     79     88
+//   4096, 8, 2    token        8.6    8.6    8.6     10      -      -
+//                 dense          -      -     15     15     15     16
+//                 screen        13     17     18     18     19     21
+//                 before       9.8     17     17     18     18     19
+enum GateKernel { kGateToken, kGateDense, kGateDenseTopk, kGateScreen };
+GateKernel gate_kernel(int T, int d, int E, bool wanted, bool stored) {
+  // One block per token: about one round of blocks over the chip, or, with
+  // at most 16 experts (one per wave), a few. A token's E x d products at one
+  // CU's rate are worth dense's second launch from about half a million on.
+  const bool few = T <= (E <= 8 ? 1024 : E <= 16 ? 512 : 256);
+  if (few && !(stored && (long long)E * d > 512 * 1024)) return kGateToken;
+  if (E <= 16) return kGateDenseTopk;
+  if (wanted) return kGateDense;
+  // Dense costs T x E x d, the screen a pass over the gate matrix per 16
+  // tokens of a CU: equal near 1300 tokens of 256 experts, 2100 of 64.
+  const long long te = (long long)T * E;
+  if (stored && te <= (E <= 128 ? 1 << 17 : 1 << 18)) return kGateDense;
+  // The screen addresses 256 experts' rows at once with 31-bit byte offsets.
+  if (512LL * d < (1LL << 31)) return kGateScreen;
+  return stored ? kGateDense : kGateToken;
+}
+
 }  // namespace
 
 hipError_t launch_gate_topk(const uint16_t* x, const uint16_t* wg, const float* logits_in, int T,
                             int d, int E, int k, float* logits_out, int32_t* ids, float* w,
-                            hipStream_t stream) {
+                            hipStream_t stream, float* scratch) {
   if (T == 0) return hipSuccess;
-  if (logits_in && E <= 256 && k <= 16 && T >= 4096) {
-    const int per_block = 4 * kRowTokens;  // 4 waves of 4 tokens
-    const dim3 grid((T + per_block - 1) / per_block);
-    if (E <= 64)
-      hipLaunchKernelGGL(logits_topk_rows_kernel<4>, grid, dim3(256), 0, stream, logits_in, T, E, k,
-                         ids, w);
-    else if (E <= 128)
-      hipLaunchKernelGGL(logits_topk_rows_kernel<8>, grid, dim3(256), 0, stream, logits_in, T, E, k,
-                         ids, w);
-    else
-      hipLaunchKernelGGL(logits_topk_rows_kernel<16>, grid, dim3(256), 0, stream, logits_in, T, E,
-                         k, ids, w);
-  } else if (logits_in) {
-    hipLaunchKernelGGL(logits_topk_kernel, dim3((T + kWaves - 1) / kWaves), dim3(256), 0, stream,
-                       logits_in, T, E, k, ids, w);
-  } else if ((long)E * d <= kStageElemsF32 && E <= kStagedMaxE) {
-    hipLaunchKernelGGL(gate_weights_topk_kernel<2>, dim3((T + kStagedWaves - 1) / kStagedWaves),
-                       dim3(64 * kStagedWaves), 0, stream, x, wg, T, d, E, k, logits_out, ids, w);
-  } else if ((long)E * d <= kStageElems && E <= kStagedMaxE) {
-    hipLaunchKernelGGL(gate_weights_topk_kernel<1>, dim3((T + kStagedWaves - 1) / kStagedWaves),
-                       dim3(64 * kStagedWaves), 0, stream, x, wg, T, d, E, k, logits_out, ids, w);
-  } else {
-    hipLaunchKernelGGL(gate_weights_topk_kernel<0>, dim3((T + kWaves - 1) / kWaves), dim3(256),
-                       0, stream, x, wg, T, d, E, k, logits_out, ids, w);
+  if (logits_in) {
+    launch_logits_topk(logits_in, T, E, k, ids, w, stream);
+    return hipGetLastError();
+  }
+  float* const logits = logits_out ? logits_out : scratch;
+  switch (gate_kernel(T, d, E, logits_out != nullptr, logits != nullptr)) {
+    case kGateToken:
+      // 8 waves, so that more blocks share a CU, where that is a wave per expert.
+      if (E <= 8)
+        hipLaunchKernelGGL(gate_token_topk_kernel<8>, dim3(T), dim3(64 * 8), 0, stream, x, wg, d, E,
+                           k, logits_out, ids, w);
+      else
+        hipLaunchKernelGGL(gate_token_topk_kernel<16>, dim3(T), dim3(64 * 16), 0, stream, x, wg, d,
+                           E, k, logits_out, ids, w);
+      break;
+    case kGateDense:
+      hipLaunchKernelGGL(gate_logits_f64_kernel<false>, dim3((T + 15) / 16, (E + 15) / 16),
+                         dim3(64 * kDenseWaves), 0, stream, x, wg, T, d, E, k, logits, ids, w);
+      launch_logits_topk(logits, T, E, k, ids, w, stream);
+      break;
+    case kGateDenseTopk:
+      hipLaunchKernelGGL(gate_logits_f64_kernel<true>, dim3((T + 15) / 16), dim3(64 * kDenseWaves),
+                         0, stream, x, wg, T, d, E, k, logits_out, ids, w);
+      break;
+    case kGateScreen:
+      if (E > 512) launch_screen<1, 4>(x, wg, T, d, E, k, ids, w, stream);
+      else if (E > 256) launch_screen<1, 2>(x, wg, T, d, E, k, ids, w, stream);
+      else if (E > 128) launch_screen<1, 1>(x, wg, T, d, E, k, ids, w, stream);
+      else if (E > 64) launch_screen<2, 1>(x, wg, T, d, E, k, ids, w, stream);
+      else launch_screen<4, 1>(x, wg, T, d, E, k, ids, w, stream);
+      break;
   }
   return hipGetLastError();
 }

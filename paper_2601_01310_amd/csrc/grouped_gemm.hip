@@ -90,16 +90,6 @@ __device__ __forceinline__ int swz(int r) {
   return ((r >> 1) ^ (r >> 3)) & 3;
 }
 
-#define TG_WAIT_VM(n) \
-  __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
-
-__device__ __forceinline__ void block_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-typedef __attribute__((address_space(3))) uint16_t lds_u16;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -109,21 +99,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // expression, so all tile shapes give the same bits.
 __device__ __forceinline__ float swiglu(float g, float u) {
   return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
-}
-
-// One 16-byte global -> LDS transfer per lane; the wave's 64 chunks land at
-// consecutive 16-byte positions starting at the (wave-uniform) `lds` row.
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t rsrc, lds_u16* lds, int voffset,
-                                           int soffset) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds, 16,
-                                           voffset, soffset, 0, 0);
-#endif
-}
-
-// Raw buffer resource over [base, base + bytes); loads beyond it return 0.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
 
 // Resource over the weight rows b_row0 .. end of slot `slot` (NW rows of K

@@ -218,9 +218,13 @@ tg_status ew_forward(const tg_ew_args* a, void* ws, size_t ws_bytes, void* strea
     if (events && e == hipSuccess) e = hipEventRecord(static_cast<hipEvent_t>(events[i]), s);
   };
   mark(0);
+  // h is written by the gate/up GEMM only: until then its place can hold the
+  // logits, when they fit.
+  const bool fits = (size_t)a->E * sizeof(float) <= (size_t)a->k * a->I * sizeof(uint16_t);
   if (e == hipSuccess)
     e = tg::launch_gate_topk(a->w_gate ? a->x : nullptr, a->w_gate, a->logits_in, a->T, a->d, a->E,
-                             a->k, nullptr, ids, w, s);
+                             a->k, nullptr, ids, w, s,
+                             fits ? reinterpret_cast<float*>(L.h) : nullptr);
   mark(1);
   // The gate/up GEMM reads the token rows in place through perm when x is
   // addressable with 32-bit byte offsets; otherwise they are gathered first.

@@ -35,9 +35,10 @@ inline void sched_carve(void* base, GemmSched* gateup, GemmSched* down) {
   down->claims = b ? reinterpret_cast<int32_t*>(b + 64) : nullptr;
 }
 
+// scratch (optional): memory for T * E floats that the call may overwrite.
 hipError_t launch_gate_topk(const uint16_t* x, const uint16_t* wg, const float* logits_in, int T,
                             int d, int E, int k, float* logits_out, int32_t* ids, float* w,
-                            hipStream_t stream);
+                            hipStream_t stream, float* scratch = nullptr);
 
 // Pairs are processed in at most kDispatchChunks chunks (each a multiple of
 // 256 pairs, at least 256); the workspace holds one S-wide histogram and one

@@ -1,0 +1,142 @@
+"""The gate's kernels in weight mode: ids and weights must be the bits that the
+float64 logits of every expert give.
+
+A call that asks for the logits forms all of them in float64 (one token per
+block for few tokens, else on the matrix cores); the same call without them
+screens the experts on the matrix cores first. Inputs where
+the screen says little (large terms that cancel, equal experts, equal logits
+at the k-th place, overflowing magnitudes, denormals) are among them.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_ew as O
+from paper_2601_01310_amd import synth, tg
+from tests import _gate_cases as C
+from tests._util import host, u16
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _run(x, w, k, want_logits):
+    T, d = x.shape
+    E = w.shape[0]
+    logits = torch.empty((T, E), dtype=torch.float32, device=DEV) if want_logits else None
+    ids = torch.full((T, k), -7, dtype=torch.int32, device=DEV)
+    tw = torch.full((T, k), -7.0, dtype=torch.float32, device=DEV)
+    tg.tg_gate_topk(x, w, None, T, d, E, k, logits, ids, tw)
+    torch.cuda.synchronize()
+    return (None if logits is None else host(logits)), host(ids), host(tw)
+
+
+def _same(x, w, k):
+    logits, ids, tw = _run(x, w, k, True)
+    _, ids2, tw2 = _run(x, w, k, False)
+    assert np.array_equal(ids, O.topk(logits, k))
+    assert np.array_equal(ids2, ids)
+    assert np.array_equal(tw2.view(np.uint32), tw.view(np.uint32))
+
+
+def _normal(T, d, E, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    x = torch.randn((T, d), generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn((E, d), generator=g, device=DEV) * 0.02).to(torch.bfloat16)
+    return x, w
+
+
+# Up to 256 tokens (512 with at most 16 experts, 1024 with 8) a block per
+# token; beyond, up to 16 experts by one dense block per 16 tokens, else the
+# screen in every number of pieces and groups (E <= 64, 128, 256, 512,
+# 1024), tiles of 16 experts that are partial, token tails, row lengths off
+# the stages' 64 to 256 elements, the largest E and k.
+@pytest.mark.parametrize("T,d,E,k", [
+    (1, 7168, 256, 8), (3, 128, 5, 5), (256, 448, 40, 5), (1024, 192, 8, 4), (512, 192, 16, 4),
+    (257, 7168, 256, 8), (1025, 4096, 16, 1), (1030, 256, 8, 2), (1033, 320, 3, 3), (513, 7168, 16, 8),
+    (299, 3136, 17, 17), (276, 1856, 64, 6), (321, 960, 65, 3), (287, 4160, 128, 32),
+    (274, 448, 129, 8), (273, 1024, 160, 6), (296, 2112, 257, 9), (291, 192, 512, 32),
+    (306, 128, 1000, 8), (289, 7168, 1024, 32)])
+def test_screen_gives_the_bits_of_all_float64_logits(T, d, E, k):
+    print(f"[gpu] gate screen T={T} d={d} E={E} k={k}", flush=True)
+    x, w = _normal(T, d, E, T * 7 + d + E)
+    _same(x, w, k)
+
+
+@pytest.mark.parametrize("T,E,I", [(300, 64, 128), (1030, 17, 192), (700, 256, 128)])
+def test_the_forward_gates_as_the_gate_does(T, E, I):
+    """The forward may form the logits in its workspace first."""
+    print(f"[gpu] gate in the forward T={T} E={E}", flush=True)
+    wl = synth.make_custom(T=T, d=256, E=E, k=2, I=I, n_local=2, shadow_experts=[0],
+                           gate="weights", seed=T, device=DEV)
+    f = tg.EwForward(wl)
+    f()
+    _, ids, tw = _run(wl.x, wl.wg, 2, False)
+    logits = O.gate_logits(u16(wl.x), u16(wl.wg))
+    assert np.array_equal(ids, O.topk(logits, 2))
+    assert np.array_equal(host(f.topk_ids), ids)
+    assert np.array_equal(host(f.topk_w).view(np.uint32), tw.view(np.uint32))
+
+
+@pytest.mark.parametrize("E,k", [(64, 4), (100, 8), (256, 8)])
+def test_equal_experts_and_ties(E, k):
+    """Copies of one gate row tie exactly: the lower ids win."""
+    print(f"[gpu] gate screen ties E={E}", flush=True)
+    x, w = _normal(293, 2048, E, 5)
+    w[E // 2:] = w[:E - E // 2]      # every expert twice
+    w[3:E:9] = w[3]                  # and one of them many times
+    _same(x, w, k)
+    w[:] = w[0]                      # all of them: every expert is a candidate
+    _same(x, w, k)
+
+
+def test_cancelling_terms_at_float32_midpoints():
+    """Rows whose exact logits lie at float32 midpoints behind a +1024 / -1024
+    pair, which a float32 sum cannot tell apart."""
+    print("[gpu] gate screen midpoints", flush=True)
+    xb, wb, expected, _ = C.engineered(40, 32, 4096, seed=11)
+    xb, expected = np.tile(xb, (8, 1)), np.tile(expected, (8, 1))  # 320 tokens
+    x = torch.from_numpy(xb.view(np.int16)).view(torch.bfloat16).to(DEV)
+    w = torch.from_numpy(wb.view(np.int16)).view(torch.bfloat16).to(DEV)
+    logits, _, _ = _run(x, w, 6, True)
+    assert np.array_equal(logits.view(np.uint32), expected.view(np.uint32))
+    _, ids, tw = _run(x, w, 6, False)
+    r_ids = O.topk(expected, 6)
+    assert np.array_equal(ids, r_ids)
+    assert np.abs(tw - O.gate_weights(expected, r_ids)).max() <= 1e-6
+
+
+@pytest.mark.parametrize("what", ["zero", "denormal", "huge", "overflow", "one_sided"])
+def test_extreme_magnitudes(what):
+    print(f"[gpu] gate screen {what}", flush=True)
+    x, w = _normal(280, 1024, 96, 3)
+    if what == "zero":
+        x[::2] = 0
+    elif what == "denormal":        # products near and below the smallest float32
+        x *= 2.0 ** -120
+        w[:, ::2] *= 2.0 ** -20
+        w[:, 1::2] = (w[:, 1::2].float() * 2.0 ** -125).to(torch.bfloat16)
+    elif what == "huge":            # near float32's end, finite sums
+        x *= 2.0 ** 100
+        w *= 2.0 ** 15
+    elif what == "overflow":        # products past float32 that cancel in float64
+        # (no small values: every float64 sum is exact, multiples of 2^82 below 2^132)
+        x[x.abs() < 2.0 ** -4] = 0
+        w[w.abs() < 2.0 ** -10] = 0
+        x, w = x * 2.0 ** 55, w * 2.0 ** 55
+        x[:, 0] = x[:, 1] = w[:, 0] = 2.0 ** 65
+        w[:, 1] = -(2.0 ** 65)
+    else:                           # all products of one sign
+        x, w = x.abs(), w.abs()
+    _same(x, w, 8)
+
+
+def test_screen_matches_the_oracle():
+    print("[gpu] gate screen oracle", flush=True)
+    x, w = _normal(300, 7168, 256, 77)
+    _, ids, tw = _run(x, w, 8, False)
+    logits = O.gate_logits(u16(x), u16(w))
+    r = O.topk(logits, 8)
+    assert np.array_equal(ids, r)
+    assert np.abs(tw - O.gate_weights(logits, r)).max() <= 1e-6
