@@ -128,9 +128,10 @@ tg_status tg_expert_ffn_grouped(const uint16_t* x_perm, const int32_t* slot_offs
  *
  *   TG_TILES_AUTO  (default) each GEMM launch chooses on the device from
  *                  the slot counts: 32-row tiles for batches whose slots
- *                  hold few rows (decode steps, a single small expert
- *                  batch), 256-row tiles otherwise;
- *   TG_TILES_SMALL every tile 32 rows;
+ *                  hold few rows (decode steps), 256-row tiles for large
+ *                  batches, and shapes between them where those leave the
+ *                  chip partly idle (few experts, some tens of rows each);
+ *   TG_TILES_SMALL every tile 32 rows (32 x 256 and 32 x 128);
  *   TG_TILES_FULL  every tile 256 rows (partial last rounds of the down
  *                  projection still split into 128 x 128 quarters).
  *

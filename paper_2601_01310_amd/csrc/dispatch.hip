@@ -27,6 +27,7 @@
 // copy is fully coalesced without staging).
 #include "tg_device.h"
 #include "tg_launch.h"
+#include "tg_shapes.h"
 
 namespace tg {
 namespace {
@@ -97,6 +98,23 @@ __device__ __forceinline__ uint64_t same_slot_lanes(int s, int sbits) {
   return s >= 0 ? eq : 0;
 }
 
+// Plans both GEMMs of the call (wave 0 the gate/up GEMM, wave 1 the down
+// GEMM; other waves have nothing to do here). count(s): rows of slot s.
+template <typename Count>
+__device__ __forceinline__ void plan_gemms(int which, int S, Count count, int32_t* sched,
+                                           const GemmDims& g) {
+  if (which > 1) return;
+  const Census cs = census(S, count);
+  const int shape = which == 0 ? choose_shape<true, false>(cs, g.grid, g.d, g.I)
+                               : choose_shape<false, true>(cs, g.grid, g.I, g.d);
+  store_plan(sched + 16 * which, cs, shape);
+}
+
+// The claim counters of both GEMMs start at zero.
+__device__ __forceinline__ void zero_claims(int32_t* sched, int tid) {
+  if (tid < 2 * kSchedPlan) sched[tid < kSchedPlan ? tid : tid - kSchedPlan + 16] = 0;
+}
+
 // REPLAY: `prior` holds the first pass's slot of every pair; out_slot gets
 // the slot the pair is recomputed on, or -1 when its first-pass result still
 // stands (slot alive), it is outside the batch (-2), or no candidate is live.
@@ -105,7 +123,7 @@ __global__ __launch_bounds__(kBlock) void remap_count_kernel(
     const int32_t* __restrict__ ids, int npairs, int k, const int32_t* __restrict__ ert, int E,
     int R, const uint8_t* __restrict__ alive, int S, const uint8_t* __restrict__ token_valid,
     const int32_t* __restrict__ prior, int32_t* __restrict__ out_slot, int32_t* __restrict__ hist,
-    int32_t* __restrict__ unserved_chunk, int chunk, uint32_t* __restrict__ zero, int zero_words) {
+    int32_t* __restrict__ unserved_chunk, int chunk, int32_t* __restrict__ sched) {
   __shared__ int h[kMaxS];
   __shared__ int nu;
   for (int s = threadIdx.x; s < S; s += kBlock) h[s] = 0;
@@ -125,9 +143,7 @@ __global__ __launch_bounds__(kBlock) void remap_count_kernel(
   __syncthreads();
   for (int s = threadIdx.x; s < S; s += kBlock) hist[(size_t)s * gridDim.x + blockIdx.x] = h[s];
   if (threadIdx.x == 0) unserved_chunk[blockIdx.x] = nu;
-  // The GEMMs' schedule area of this call starts at zero.
-  if (zero && blockIdx.x == 0)
-    for (int i = threadIdx.x; i < zero_words; i += kBlock) zero[i] = 0;
+  if (sched && blockIdx.x == 0) zero_claims(sched, threadIdx.x);
 }
 
 // One block of 1024 threads (16 waves). hist[s * nchunks + c] holds the
@@ -211,18 +227,25 @@ __device__ __forceinline__ int wave_sum_int(int v) {
 // derives what it needs itself (its chunk's position in each slot and the
 // slot offsets, from all of hist; for small S * nchunks this is cheaper
 // than a launch); block 0 also writes counts, offsets, the unserved count
-// and the total. sbits: bits of the largest slot index.
+// and the total. sbits: bits of the largest slot index. With a schedule area
+// one block more than there are chunks is launched, which plans the GEMMs.
 template <bool SCAN>
 __global__ __launch_bounds__(kBlock) void scatter_kernel(
     const int32_t* __restrict__ pair_slot, int npairs, int S, int nchunks, int sbits,
     const int32_t* __restrict__ hist, const int32_t* __restrict__ unserved_chunk,
     int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
     int32_t* __restrict__ n_unserved, int32_t* __restrict__ total_out,
-    int32_t* __restrict__ perm, int32_t* __restrict__ pair_row, int chunk) {
+    int32_t* __restrict__ perm, int32_t* __restrict__ pair_row, int chunk,
+    int32_t* __restrict__ sched, GemmDims dims) {
   constexpr int kWaves = kBlock / kWave;
   __shared__ int cnt[kWaves][kMaxS];
   const int wave = threadIdx.x / kWave;
   const int lane = lane_id();
+  const bool planner = (int)blockIdx.x == nchunks;
+  if (!SCAN && planner) {
+    plan_gemms(wave, S, [&](int s) { return offsets[s + 1] - offsets[s]; }, sched, dims);
+    return;
+  }
   // The chunk's pairs are split evenly (in multiples of 64) over the waves.
   const int c0 = blockIdx.x * chunk;
   const int n_c = min(chunk, npairs - c0);
@@ -261,6 +284,10 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(
     }
   }
   __syncthreads();
+  if (SCAN && planner) {
+    plan_gemms(wave, S, [&](int s) { return tot[s]; }, sched, dims);
+    return;
+  }
   if (SCAN) {
     // Exclusive scan of the slot totals: thread i holds slots 4i .. 4i+3.
     int v[4], sum = 0;
@@ -360,12 +387,13 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
     const uint8_t* __restrict__ token_valid, const int32_t* __restrict__ prior,
     int32_t* __restrict__ out_slot, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
     int32_t* __restrict__ perm, int32_t* __restrict__ pair_row, int32_t* __restrict__ n_unserved,
-    int32_t* __restrict__ total_out, uint32_t* __restrict__ zero, int zero_words) {
+    int32_t* __restrict__ total_out, int32_t* __restrict__ sched, GemmDims dims) {
   constexpr int kWaves = kOneBlock / kWave;
   // cnt[w][s]: pairs of wave w on slot s in the current group of 1024, then
   // their first row; 0 wherever wave w has no pair on s.
   __shared__ int cnt[kWaves][kMaxS];
   __shared__ int run[kMaxS];
+  __shared__ int tot[kMaxS];  // pairs of each slot
   __shared__ int ert_s[kMaxErt];
   __shared__ uint8_t alive_s[kMaxS];
   __shared__ int wsum[kWaves];
@@ -443,7 +471,10 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
   if (lane == kWave - 1) wsum[wave] = incl;
   __syncthreads();
   for (int w = 0; w < wave; ++w) incl += wsum[w];
-  if (tid < S) run[tid] = incl - total;  // next row of the slot
+  if (tid < S) {
+    run[tid] = incl - total;  // next row of the slot
+    tot[tid] = total;
+  }
 
   int my_row[kSmallPer];
 #pragma unroll
@@ -494,9 +525,14 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
       if (my_row[i] >= 0) perm[my_row[i]] = p;
     }
   }
-  // The GEMMs' schedule area of this call starts at zero.
-  if (zero)
-    for (int j = tid; j < zero_words; j += kOneBlock) zero[j] = 0;
+  if (sched) {
+    zero_claims(sched, tid);
+    // The last two waves, which have the fewest pairs, plan the GEMMs. (The
+    // totals were written before the barriers of the first ranked group; a
+    // batch without pairs has none.)
+    if (npairs == 0) __syncthreads();
+    plan_gemms(kWaves - 1 - wave, S, [&](int s) { return tot[s]; }, sched, dims);
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void gather_kernel(const uint4* __restrict__ x,
@@ -536,9 +572,8 @@ hipError_t remap_dispatch(bool replay, const int32_t* ids, int T, int k, const i
                           const int32_t* prior, const uint16_t* x, int d, int32_t* pair_slot,
                           int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* pair_row,
                           uint16_t* x_perm, int32_t* n_unserved, int32_t* total_out, void* ws,
-                          hipStream_t stream, void* sched_area) {
-  uint32_t* const zero = static_cast<uint32_t*>(sched_area);
-  const int zero_words = sched_area ? (int)(kSchedBytes / 4) : 0;
+                          hipStream_t stream, void* sched_area, const GemmDims& dims) {
+  int32_t* const sched = static_cast<int32_t*>(sched_area);
   const int npairs = T * k;
   const int chunk = dispatch_chunk(npairs);
   const int nchunks = (npairs + chunk - 1) / chunk;
@@ -550,12 +585,12 @@ hipError_t remap_dispatch(bool replay, const int32_t* ids, int T, int k, const i
     if (replay)
       hipLaunchKernelGGL(dispatch_one_block_kernel<true>, dim3(1), dim3(kOneBlock), 0, stream, ids,
                          npairs, k, ert, E, R, alive, S, sbits, nullptr, prior, pair_slot, counts,
-                         offsets, perm, pair_row, n_unserved, total_out, zero, zero_words);
+                         offsets, perm, pair_row, n_unserved, total_out, sched, dims);
     else
       hipLaunchKernelGGL(dispatch_one_block_kernel<false>, dim3(1), dim3(kOneBlock), 0, stream,
                          ids, npairs, k, ert, E, R, alive, S, sbits, token_valid, nullptr,
-                         pair_slot, counts, offsets, perm, pair_row, n_unserved, total_out, zero,
-                         zero_words);
+                         pair_slot, counts, offsets, perm, pair_row, n_unserved, total_out, sched,
+                         dims);
     if (x_perm && npairs > 0) {
       const int nch = d / 8;
       const long maxq = (long)npairs * nch;
@@ -571,11 +606,11 @@ hipError_t remap_dispatch(bool replay, const int32_t* ids, int T, int k, const i
     if (replay)
       hipLaunchKernelGGL(remap_count_kernel<true>, dim3(nchunks), dim3(kBlock), 0, stream, ids,
                          npairs, k, ert, E, R, alive, S, nullptr, prior, pair_slot, hist,
-                         unserved_chunk, chunk, zero, zero_words);
+                         unserved_chunk, chunk, sched);
     else
       hipLaunchKernelGGL(remap_count_kernel<false>, dim3(nchunks), dim3(kBlock), 0, stream, ids,
                          npairs, k, ert, E, R, alive, S, token_valid, nullptr, pair_slot, hist,
-                         unserved_chunk, chunk, zero, zero_words);
+                         unserved_chunk, chunk, sched);
   }
   // A small histogram is scanned by every scatter block (one launch less).
   const bool fused_scan = nchunks > 0 && (long)S * nchunks <= (long)kFusedScanHist;
@@ -583,14 +618,15 @@ hipError_t remap_dispatch(bool replay, const int32_t* ids, int T, int k, const i
     hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, stream, hist, unserved_chunk, nchunks,
                        S, counts, offsets, n_unserved, total_out);
   if (nchunks > 0) {
+    const dim3 grid(nchunks + (sched ? 1 : 0));
     if (fused_scan)
-      hipLaunchKernelGGL(scatter_kernel<true>, dim3(nchunks), dim3(kBlock), 0, stream, pair_slot,
-                         npairs, S, nchunks, sbits, hist, unserved_chunk, counts, offsets,
-                         n_unserved, total_out, perm, pair_row, chunk);
+      hipLaunchKernelGGL(scatter_kernel<true>, grid, dim3(kBlock), 0, stream, pair_slot, npairs, S,
+                         nchunks, sbits, hist, unserved_chunk, counts, offsets, n_unserved,
+                         total_out, perm, pair_row, chunk, sched, dims);
     else
-      hipLaunchKernelGGL(scatter_kernel<false>, dim3(nchunks), dim3(kBlock), 0, stream, pair_slot,
-                         npairs, S, nchunks, sbits, hist, unserved_chunk, counts, offsets,
-                         n_unserved, total_out, perm, pair_row, chunk);
+      hipLaunchKernelGGL(scatter_kernel<false>, grid, dim3(kBlock), 0, stream, pair_slot, npairs, S,
+                         nchunks, sbits, hist, unserved_chunk, counts, offsets, n_unserved,
+                         total_out, perm, pair_row, chunk, sched, dims);
     if (x_perm) {
       const int nch = d / 8;
       const long maxq = (long)npairs * nch;
@@ -611,10 +647,10 @@ hipError_t launch_remap_dispatch(const int32_t* ids, int T, int k, const int32_t
                                  int32_t* pair_slot, int32_t* counts, int32_t* offsets,
                                  int32_t* perm, int32_t* pair_row, uint16_t* x_perm,
                                  int32_t* n_unserved, void* ws, hipStream_t stream,
-                                 const uint8_t* token_valid, void* sched_area) {
+                                 const uint8_t* token_valid, void* sched_area, GemmDims dims) {
   return remap_dispatch(false, ids, T, k, ert, E, R, alive, S, token_valid, nullptr, x, d,
                         pair_slot, counts, offsets, perm, pair_row, x_perm, n_unserved, nullptr,
-                        ws, stream, sched_area);
+                        ws, stream, sched_area, dims);
 }
 
 hipError_t launch_replay_dispatch(const int32_t* ids, int T, int k, const int32_t* ert, int E,
@@ -622,10 +658,10 @@ hipError_t launch_replay_dispatch(const int32_t* ids, int T, int k, const int32_
                                   const uint16_t* x, int d, int32_t* replay_slot, int32_t* counts,
                                   int32_t* offsets, int32_t* perm, int32_t* replay_row,
                                   uint16_t* x_perm, int32_t* n_unserved, int32_t* n_replayed,
-                                  void* ws, hipStream_t stream, void* sched_area) {
+                                  void* ws, hipStream_t stream, void* sched_area, GemmDims dims) {
   return remap_dispatch(true, ids, T, k, ert, E, R, alive, S, nullptr, prior_slot, x, d,
                         replay_slot, counts, offsets, perm, replay_row, x_perm, n_unserved,
-                        n_replayed, ws, stream, sched_area);
+                        n_replayed, ws, stream, sched_area, dims);
 }
 
 }  // namespace tg

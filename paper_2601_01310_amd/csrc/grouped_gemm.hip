@@ -36,22 +36,24 @@
 // no data exchange.
 //
 // Tile shapes: one persistent kernel (one block per CU) runs every launch
-// in one of two shapes, chosen on the device from the slot counts, so that
-// the host never reads them: 256 x 256 tiles with 4 waves (one per SIMD,
-// 128 x 128 each) for batches that fill the MFMA units, walked with the DMA
-// pipeline running on across tiles (the gate/up results written straight
-// from the accumulators, the down projection's staged in LDS and written as
-// whole 128-byte lines); or 32-row tiles with 4 waves (32 x 256 in the gate/up
-// projection, 32 x 128 in the down projection), where a launch mostly
-// streams weights (decode steps, a single small expert batch) and a 256-row
-// tile would stage and multiply mostly zero rows (results staged through
-// each wave's own LDS region and written as 16-byte row segments). The
-// 32-row shape runs when its rounds of tiles over the grid cost less, at
-// about two thirds of a 256-row round each; in the down projection, whose
-// partial last round of 256 x 256 tiles runs as 128 x 128 quarter tiles
-// (keeping the CUs busy with few tiles), when no slot holds more than 32
-// rows or the 32-row tiles fit in one round. All shapes give identical
-// bits, so the choice never changes a result.
+// in one of nine shapes, chosen on the device from the slot counts
+// (tg_shapes.h), so that the host never reads them: 256 x 256 tiles with 4
+// waves (one per SIMD, 128 x 128 each) for batches that fill the MFMA units,
+// walked with the DMA pipeline running on across tiles (the gate/up results
+// written straight from the accumulators, the down projection's staged in LDS
+// and written as whole 128-byte lines); 32-row tiles with 4 waves (32 x 256
+// in the gate/up projection, 32 x 128 in the down projection), where a launch
+// mostly streams weights (decode steps); or 32, 64 or 128 rows by 32 to 256
+// weight rows, each tile with its own ring of stage buffers, where the others
+// leave CUs without a tile or mostly multiply zero rows (a single expert's
+// batch, a replay, a small model, some tens of rows per slot). Results of the
+// ring shapes are staged through each wave's own LDS region and written as
+// 16-byte row segments. All shapes give identical bits, so the choice never
+// changes a result. Measured, us, gate/up + down, before (the first two shapes
+// only) -> now: one DeepSeek-V3 expert (d 7168, I 2048) of 48 rows 84 + 17 ->
+// 24 + 13, of 1024 rows 145 + 46 -> 73 + 38; one Mixtral expert (d 4096,
+// I 14336) of one row 61 + 77 -> 52 + 36, of 333 rows 95 + 119 -> 95 + 81;
+// four DeepSeek-V3 experts of 32 rows 92 + 32 -> 43 + 32.
 //
 // Tile order: the tiles of one launch are enumerated slot by slot, then by
 // weight panel (n), then by row block (m), so consecutive tiles share a
@@ -75,11 +77,13 @@
 
 #include "tg_device.h"
 #include "tg_launch.h"
+#include "tg_shapes.h"
 
 namespace tg {
 namespace {
 
 constexpr int kXcds = 8;
+constexpr int kSmemElems = 80 * 1024;  // the whole LDS of a CU, 160 KB
 constexpr int kDynRounds = 3;  // last rounds of each XCD's range that are claimed, not dealt
 
 // XOR swizzle of the 16-byte chunks of a staged row (CH chunks per row);
@@ -101,44 +105,17 @@ __device__ __forceinline__ float swiglu(float g, float u) {
   return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
 
-// Resource over the weight rows b_row0 .. end of slot `slot` (NW rows of K
-// elements per slot); empty when b_row0 lies past the slot's last row.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rsrc(const uint16_t* B, int slot, int NW,
-                                                              size_t b_row0, int K) {
+// Bytes of the weight rows b_row0 .. end of slot `slot` (NW rows of K
+// elements per slot); none when b_row0 lies past the slot's last row.
+__device__ __forceinline__ uint32_t weight_bytes(int slot, int NW, size_t b_row0, int K) {
   const size_t end = (size_t)(slot + 1) * NW;
   const size_t bytes = b_row0 < end ? (end - b_row0) * K * 2 : 0;
-  return make_rsrc(B + b_row0 * K, (uint32_t)min((size_t)0x7fffffff, bytes));
+  return (uint32_t)min((size_t)0x7fffffff, bytes);
 }
 
 struct TileInfo {
   int slot, row0, rows, nt;
 };
-
-// Row-block counts of one launch at both tile heights, and its largest slot
-// (every lane gets the results).
-struct Census {
-  int full, small, max_rows;  // 256-row tiles, 32-row tiles (times NTx), largest count
-};
-__device__ __forceinline__ Census census(const int32_t* __restrict__ offsets, int S, int NTx) {
-  const int lane = lane_id();
-  int full = 0, small = 0, mx = 0;
-  for (int base = 0; base < S; base += kWave) {
-    const int s = base + lane;
-    const int cnt = (s < S) ? offsets[s + 1] - offsets[s] : 0;
-    int f = (cnt + 255) / 256, q = (cnt + 31) / 32, m = cnt;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      f += __shfl_xor(f, off);
-      q += __shfl_xor(q, off);
-      m = max(m, __shfl_xor(m, off));
-    }
-    full += f;
-    small += q;
-    mx = max(mx, m);
-  }
-  return {__builtin_amdgcn_readfirstlane(full) * NTx,
-          __builtin_amdgcn_readfirstlane(small) * NTx, __builtin_amdgcn_readfirstlane(mx)};
-}
 
 // Tile L of BMx-row tiles in the order slot, panel, row block:
 // its slot, first row, row count, panel and row-block index.
@@ -190,43 +167,46 @@ __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets, i
 // GATHER: the activation rows are not pre-permuted; row r of the grouped
 // matrix is row perm[r] / kq of A (the token of routed pair perm[r]), read
 // in place through a buffer resource over all A_rows rows of A.
-template <int BM, int BN, int BK, int WM, int WN, bool SWIGLU, bool GATHER, int NBUF>
+template <int BM, int BN, int WM, int WN, int SUB, int NBUF, bool SWIGLU, bool GATHER>
 __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileInfo& tile,
                                           const uint16_t* __restrict__ A,
                                           const uint16_t* __restrict__ B, int K, int NW, int I,
                                           uint16_t* __restrict__ C, int ldc,
                                           const int32_t* __restrict__ perm, int kq, int A_rows) {
-  constexpr int NWAVE = WM * WN;
+  constexpr int BK = 64, NWAVE = 4;
   constexpr int MB = BM / WM / 32;          // 32-row blocks per wave
   constexpr int NB = BN / WN / 32;          // 32-col blocks per wave
+  // With one weight block per wave, SwiGLU's holds 16 gate and 16 up rows.
+  constexpr bool PACK = SWIGLU && NB == 1;
   constexpr int CH = BK / 8;                // 16-byte chunks per staged row
   constexpr int RPI = 64 / CH;              // rows per load instruction (64 lanes x 16 B)
   constexpr int AI = BM / NWAVE / RPI;      // A load instructions per wave per stage
   constexpr int BI = BN / NWAVE / RPI;      // B load instructions per wave per stage
-  constexpr int A_ST = BM * BK, B_ST = BN * BK;  // elements per stage buffer
+  constexpr int A_ST = SUB * BM * BK, B_ST = SUB * BN * BK;  // elements per stage buffer
   constexpr int WOUT = SWIGLU ? BN / 2 / WN : BN / WN;  // output columns per wave
   constexpr int WP = WOUT + 8;
-  static_assert(MB >= 1 && NB >= 1 && AI >= 1 && BI >= 1 && (BK == 32 || BK == 64), "tile");
-  static_assert(!SWIGLU || NB % 2 == 0, "gate/up halves");
-  static_assert(NBUF >= 2 && (NBUF - 2) * (AI + BI) <= 63, "ring depth within the wait count");
-  static_assert(NWAVE * 32 * WP <= NBUF * (A_ST + B_ST), "epilogue fits in the stage buffers");
+  static_assert(MB >= 1 && NB >= 1 && AI >= 1 && BI >= 1 && WM * WN <= NWAVE, "tile");
+  static_assert(!SWIGLU || NB == 1 || NB % 2 == 0, "gate/up halves");
+  static_assert(NBUF >= 2 && (NBUF - 1) * SUB * (AI + BI) <= 63, "ring depth within the wait count");
+  static_assert(NBUF * (A_ST + B_ST) <= kSmemElems, "the ring fits");
+  static_assert(WM * WN * 32 * WP <= NBUF * (A_ST + B_ST), "epilogue fits in the stage buffers");
 
   const int slot = tile.slot, row0 = tile.row0, rows = tile.rows, nt = tile.nt;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = wave / WN, wn = wave % WN;  // wm >= WM: the wave only loads
 
   // Direct-to-LDS staging: load instruction i of this wave fills RPI
   // consecutive staged rows (1 KB); lane l writes chunk position l % CH of
   // row l / CH, so it fetches the global chunk that the swizzle puts there.
   const size_t b_row0 = (size_t)slot * NW + (SWIGLU ? nt * (BN / 2) : nt * BN);
   // Rows past the group's end read as zeros (their results are never stored).
-  const __amdgpu_buffer_rsrc_t a_rsrc =
-      GATHER ? make_rsrc(A, (uint32_t)A_rows * K * 2)
-             : make_rsrc(A + (size_t)row0 * K, (uint32_t)rows * K * 2);
-  const __amdgpu_buffer_rsrc_t b_rsrc = weight_rsrc(B, slot, NW, b_row0, K);
+  const uint16_t* const a_base = GATHER ? A : A + (size_t)row0 * K;
+  const uint32_t a_bytes = (uint32_t)(GATHER ? A_rows : rows) * K * 2;
+  const uint16_t* const b_base = B + b_row0 * K;
+  const uint32_t b_bytes = weight_bytes(slot, NW, b_row0, K);
   int a_off[AI], b_off[BI];  // byte offsets
 #pragma unroll
   for (int i = 0; i < AI; ++i) {
@@ -249,23 +229,29 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileInfo& tile,
   lds_u16* const smem3 = (lds_u16*)smem;
   const int a_lds = wave * (BM / NWAVE) * BK;
   const int b_lds = NBUF * A_ST + wave * (BN / NWAVE) * BK;
-#define TG_ISSUE_A(k0, buf)                                                        \
-  do {                                                                             \
-    _Pragma("unroll") for (int i = 0; i < AI; ++i)                                 \
-        load_lds16(a_rsrc, smem3 + (buf) * A_ST + a_lds + i * RPI * BK, a_off[i],   \
-                   (k0) * 2);                                                      \
-  } while (0)
-#define TG_ISSUE_B(k0, buf)                                                        \
-  do {                                                                             \
-    _Pragma("unroll") for (int i = 0; i < BI; ++i)                                 \
-        load_lds16(b_rsrc, smem3 + (buf) * B_ST + b_lds + i * RPI * BK, b_off[i],   \
-                   (k0) * 2);                                                      \
+  // Stage kt into buffer buf. A stage past the tile's last is issued through
+  // empty resources: the same count of loads, and no memory is read.
+  const int nk = K / BK;
+#define TG_ISSUE(kt, buf)                                                              \
+  do {                                                                                 \
+    _Pragma("unroll") for (int sub = 0; sub < SUB; ++sub) {                            \
+      const int k_ = (kt) * SUB + sub;                                                 \
+      const __amdgpu_buffer_rsrc_t ra_ = make_rsrc(a_base, k_ < nk ? a_bytes : 0u);    \
+      const __amdgpu_buffer_rsrc_t rb_ = make_rsrc(b_base, k_ < nk ? b_bytes : 0u);    \
+      _Pragma("unroll") for (int i = 0; i < AI; ++i)                                   \
+          load_lds16(ra_, smem3 + (buf) * A_ST + sub * BM * BK + a_lds + i * RPI * BK, \
+                     a_off[i], k_ * BK * 2);                                           \
+      _Pragma("unroll") for (int i = 0; i < BI; ++i)                                   \
+          load_lds16(rb_, smem3 + (buf) * B_ST + sub * BN * BK + b_lds + i * RPI * BK, \
+                     b_off[i], k_ * BK * 2);                                           \
+    }                                                                                  \
   } while (0)
 
   // LDS element offsets of this lane's fragments for k16 sub-step kk.
   const int khalf = lane >> 5;
   const int xrow = wm * (BM / WM) + (lane & 31);
-  const int wrow = (SWIGLU ? wn * (BN / 2 / WN) : wn * (BN / WN)) + (lane & 31);
+  const int wrow = PACK ? (lane & 16 ? BN / 2 : 0) + wn * 16 + (lane & 15)
+                        : (SWIGLU ? wn * (BN / 2 / WN) : wn * (BN / WN)) + (lane & 31);
   int xoff[BK / 16], woff[BK / 16];
 #pragma unroll
   for (int kk = 0; kk < BK / 16; ++kk) {
@@ -274,7 +260,7 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileInfo& tile,
   }
   // Weight rows of block nb relative to wrow (gate blocks, then up blocks).
   auto wblk = [](int nb) constexpr {
-    return SWIGLU ? ((nb < NB / 2) ? nb * 32 : BN / 2 + (nb - NB / 2) * 32) : nb * 32;
+    return SWIGLU && !PACK ? ((nb < NB / 2) ? nb * 32 : BN / 2 + (nb - NB / 2) * 32) : nb * 32;
   };
 
   f32x16 acc[NB][MB];
@@ -285,18 +271,17 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileInfo& tile,
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[nb][mb][r] = 0.0f;
 
-  const int nk = K / BK;
-  constexpr int KK = BK / 16;          // k16 sub-steps per stage
+  constexpr int KK = SUB * BK / 16;    // k16 sub-steps per stage
   static_assert(KK % 2 == 0, "fragment double buffering alternates within a stage");
   bf16x8 xf[2][MB], wf[2][NB];
-#define TG_FRAGS(abuf, bbuf, kk, dst)                                                  \
+#define TG_FRAGS(buf, kk, dst)                                                         \
   do {                                                                                 \
     _Pragma("unroll") for (int mb = 0; mb < MB; ++mb) xf[dst][mb] =                    \
-        *reinterpret_cast<const bf16x8*>(smem + (abuf) * A_ST + xoff[kk] +             \
-                                         mb * 32 * BK);                                \
+        *reinterpret_cast<const bf16x8*>(smem + (buf) * A_ST + (kk) / 4 * (BM * BK) +  \
+                                         xoff[(kk) % 4] + mb * 32 * BK);               \
     _Pragma("unroll") for (int nb = 0; nb < NB; ++nb) wf[dst][nb] =                    \
-        *reinterpret_cast<const bf16x8*>(smem + (bbuf) * B_ST + woff[kk] +             \
-                                         wblk(nb) * BK);                               \
+        *reinterpret_cast<const bf16x8*>(smem + (buf) * B_ST + (kk) / 4 * (BN * BK) +  \
+                                         woff[(kk) % 4] + wblk(nb) * BK);              \
   } while (0)
 #define TG_MFMAS(src)                                                                  \
   do {                                                                                 \
@@ -306,58 +291,54 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileInfo& tile,
                                                     acc[nb][mb], 0, 0, 0);             \
   } while (0)
 
-  // Prologue: stages 0 .. NBUF-1 in flight (indices past the end re-load the
-  // last stage, so every wait counts the same loads); stage 0 visible; its
-  // first fragments loaded.
-#pragma unroll
-  for (int j = 0; j < NBUF; ++j) {
-    const int k0 = min(j, nk - 1) * BK;
-    TG_ISSUE_A(k0, j);
-    TG_ISSUE_B(k0, j);
-  }
-  TG_WAIT_VM((NBUF - 1) * (AI + BI));
+  // Prologue: stages 0 .. NBUF-1 in flight; stage 0 visible; its first
+  // fragments loaded.
+#pragma unroll 1
+  for (int j = 0; j < NBUF; ++j) TG_ISSUE(j, j);
+  TG_WAIT_VM((NBUF - 1) * SUB * (AI + BI));
   block_barrier();
-  TG_FRAGS(0, 0, 0, 0);
+  const int nst = (nk + SUB - 1) / SUB;
 
   // Branch-free K loop: every iteration waits, synchronises and refills one
   // stage buffer, so each sub-step is one straight-line region. A wave whose
   // rows all lie past the group's end (in the tail tile of a slot) skips the
   // fragment reads and MFMAs but keeps its loads and barriers.
-  if (wm * (BM / WM) < rows) {
-    for (int kt = 0; kt < nk; ++kt) {
-      const int cb = kt % NBUF;
+  if (wm < WM && wm * (BM / WM) < rows) {
+    TG_FRAGS(0, 0, 0);
+    int cb = 0;  // buffer of stage kt
+    for (int kt = 0; kt < nst; ++kt) {
+      const int nb_ = cb + 1 == NBUF ? 0 : cb + 1;
 #pragma unroll
       for (int kk = 0; kk < KK - 1; ++kk) {
-        TG_FRAGS(cb, cb, kk + 1, (kk + 1) & 1);
+        TG_FRAGS(cb, kk + 1, (kk + 1) & 1);
         TG_MFMAS(kk & 1);
       }
       // Last sub-step: once every wave holds its fragments of stage kt and
       // stage kt+1 has landed, stage kt's buffer takes stage kt + NBUF, and
       // the next stage's first fragments are read while the last MFMAs run.
-      TG_WAIT_VM((NBUF - 2) * (AI + BI));
+      TG_WAIT_VM((NBUF - 2) * SUB * (AI + BI));
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
       block_barrier();
-      const int k0 = min(kt + NBUF, nk - 1) * BK;
-      TG_ISSUE_A(k0, cb);
-      TG_ISSUE_B(k0, cb);
-      TG_FRAGS((kt + 1) % NBUF, (kt + 1) % NBUF, 0, 0);
+      TG_ISSUE(kt + NBUF, cb);
+      TG_FRAGS(nb_, 0, 0);
       TG_MFMAS((KK - 1) & 1);
+      cb = nb_;
     }
   } else {
-    for (int kt = 0; kt < nk; ++kt) {
-      TG_WAIT_VM((NBUF - 2) * (AI + BI));
+    int cb = 0;
+    for (int kt = 0; kt < nst; ++kt) {
+      TG_WAIT_VM((NBUF - 2) * SUB * (AI + BI));
       block_barrier();
-      const int k0 = min(kt + NBUF, nk - 1) * BK;
-      TG_ISSUE_A(k0, kt % NBUF);
-      TG_ISSUE_B(k0, kt % NBUF);
+      TG_ISSUE(kt + NBUF, cb);
+      cb = cb + 1 == NBUF ? 0 : cb + 1;
     }
   }
   TG_WAIT_VM(0);
 #undef TG_FRAGS
 #undef TG_MFMAS
-#undef TG_ISSUE_A
-#undef TG_ISSUE_B
+#undef TG_ISSUE
   __syncthreads();
+  if (wm >= WM) return;
 
   // Epilogue. acc[nb][mb] register r of lane l holds row mb*32 + l%32 and
   // column nb*32 + 8*(r/4) + 4*(l/32) + r%4 of the wave's sub-tile. Each wave
@@ -370,20 +351,16 @@ __device__ __forceinline__ void gemm_tile(uint16_t* smem, const TileInfo& tile,
   for (int mb = 0; mb < MB; ++mb) {
     const int mm = lane & 31;
 #pragma unroll
-    for (int nb = 0; nb < (SWIGLU ? NB / 2 : NB); ++nb) {
+    for (int nb = 0; nb < (SWIGLU && !PACK ? NB / 2 : NB); ++nb) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < (PACK ? 2 : 4); ++q) {
         float v[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = 4 * q + e;
-          if (SWIGLU) {
-            const float g = acc[nb][mb][r];
-            const float u = acc[nb + NB / 2][mb][r];
-            v[e] = swiglu(g, u);
-          } else {
-            v[e] = acc[nb][mb][r];
-          }
+          if (PACK) v[e] = swiglu(acc[nb][mb][r], acc[nb][mb][r + 8]);
+          else if (SWIGLU) v[e] = swiglu(acc[nb][mb][r], acc[nb + NB / 2][mb][r]);
+          else v[e] = acc[nb][mb][r];
         }
         const int col = nb * 32 + 8 * q + 4 * (lane >> 5);
         uint2 pk;
@@ -453,54 +430,66 @@ __global__ __launch_bounds__(256) void grouped_gemm_persistent4_kernel(
   constexpr int KK = BK / 16;
   static_assert(KK == 4 && AI == 8 && BI == 8, "schedule assumes this shape");
   static_assert(!(TAIL && GATHER), "quarter tiles read pre-permuted rows");
-  __shared__ __attribute__((aligned(16))) uint16_t smem[2 * A_ST + 3 * B_ST];
+  static_assert(2 * A_ST + 3 * B_ST == kSmemElems, "stage buffers");
+  __shared__ __attribute__((aligned(16))) uint16_t smem[kSmemElems];
 
   const int per_xcd_blocks = gridDim.x / kXcds;
   const int x = blockIdx.x % kXcds, c = blockIdx.x / kXcds;
   const int G = gridDim.x;
-  const Census cs = census(offsets, S, NT);
-  bool small_tiles = policy == kTilesSmall;
-  if (policy == kTilesAuto) {
-    // Gate/up: rounds of tiles over the grid at each height; a 32-row round
-    // costs about two thirds of a 256-row round (it streams the same weight
-    // panel with an eighth of the MFMA work). Down (TAIL, 32 x 128 tiles, two
-    // per 256-column panel): 32-row tiles when no slot exceeds 32 rows, or
-    // when they fit in one round; otherwise the 256-row walk, whose partial
-    // last round splits into quarters, is faster (measured on single expert
-    // batches: a Mixtral expert's down projection of 64 to 256 rows takes
-    // 88 us in one round of 32-row tiles against 107-139 us in 256-row
-    // tiles, and 170 against 139 us at 512 rows, two rounds).
-    const int rs = (cs.small + G - 1) / G, rf = (cs.full + G - 1) / G;
-    small_tiles = TAIL ? (cs.max_rows <= 32 || 2 * cs.small <= G) : 2 * rs < 3 * rf;
+  // The plan: the dispatch's, or made here (no schedule area).
+  Census cs = {};
+  int shape;
+  if (claims) {
+    shape = claims[kSchedPlan];
+    cs.b32 = claims[kSchedPlan + 1];
+    cs.b64 = claims[kSchedPlan + 2];
+    cs.b128 = claims[kSchedPlan + 3];
+    cs.b256 = claims[kSchedPlan + 4];
+  } else {
+    cs = census(S, [&](int s) { return offsets[s + 1] - offsets[s]; });
+    shape = choose_shape<SWIGLU, TAIL>(cs, G, K, ldc);
   }
-  if (small_tiles) {
-    // 32 x 256 tiles (gate/up) or 32 x 128 tiles (down), each XCD walking
-    // one contiguous range of them. These launches stream weights; the down
-    // projection's narrower tiles split its panels finely enough to even out
-    // the blocks' shares (32 slots of d = 7168: 1792 tiles, 7 per block,
-    // instead of 896, 3 or 4 per block), and their smaller stages leave room
-    // for a deeper ring.
-    constexpr int NS = SWIGLU ? 1 : 2;  // tiles per 256-column panel
-    const int n_small = cs.small * NS;
-    const int per_s = (n_small + kXcds - 1) / kXcds;
-    const int hi_s = min(x * per_s + per_s, n_small);
+  if (policy != kTilesAuto) shape = policy == kTilesSmall ? k32 : k256;
+  // 32-row tiles and the middle shapes, each tile with its own pipeline, each
+  // XCD walking one contiguous range. These launches stream weights or have
+  // few tiles; narrower tiles split the panels finely enough to even out the
+  // blocks' shares, and their smaller stages leave room for a deeper ring.
+  // (One loop for all shapes, and no unrolled prologue: with a copy per shape
+  // the scalar registers that this code asks for cost the 256-row walk 0.6 %.)
+  if (__builtin_expect(shape != k256, 0)) {
+    const int lbm = 5 + shape_bm(shape), lcols = 5 + shape_bn<SWIGLU>(shape) - (SWIGLU ? 1 : 0);
+    const int blocks = lbm == 5 ? cs.b32 : lbm == 6 ? cs.b64 : cs.b128;
+    const int panels = (ldc + (1 << lcols) - 1) >> lcols;
+    const int n = blocks * panels;
+    const int per_s = (n + kXcds - 1) / kXcds;
+    const int hi_s = min(x * per_s + per_s, n);
     for (int q = x * per_s + c; q < hi_s; q += per_xcd_blocks) {
       TileInfo t;
       int m;
-      if (!find_tile(offsets, S, 32, NT * NS, q, &t, &m)) break;
-      t.row0 += m * 32;
-      t.rows = min(32, t.rows - m * 32);
-      if constexpr (SWIGLU)
-        gemm_tile<32, BN, BK, 1, 4, SWIGLU, GATHER, 4>(smem, t, A, B, K, NW, I, C, ldc, perm, kq,
-                                                      A_rows);
-      else
-        gemm_tile<32, BN / 2, BK, 1, 4, SWIGLU, GATHER, 8>(smem, t, A, B, K, NW, I, C, ldc, perm,
-                                                          kq, A_rows);
+      if (!find_tile(offsets, S, 1 << lbm, panels, q, &t, &m)) break;
+      t.row0 += m << lbm;
+      t.rows = min(1 << lbm, t.rows - (m << lbm));
+#define TG_TILE(BMx, BNx, WMx, WNx, SUx, NBx)                                                    \
+  gemm_tile<BMx, BNx, WMx, WNx, SUx, NBx, SWIGLU, GATHER>(smem, t, A, B, K, NW, I, C, ldc, perm, \
+                                                          kq, A_rows)
+      switch (shape) {
+        case k32x64: TG_TILE(32, 64, 1, 2, 2, 6); break;
+        case k32x32: TG_TILE(32, 32, 1, 1, 2, 10); break;
+        case k64x128: TG_TILE(64, 128, 2, 2, 1, 6); break;
+        case k64x64: TG_TILE(64, 64, 2, 2, 1, 10); break;
+        case k128x128: TG_TILE(128, 128, 2, 2, 1, 5); break;
+        case k128x64: TG_TILE(128, 64, 4, 1, 1, 6); break;
+        case k128x256: TG_TILE(128, 256, 2, 2, 1, 3); break;
+        default:
+          if constexpr (SWIGLU) TG_TILE(32, 256, 1, 4, 1, 4);
+          else TG_TILE(32, 128, 1, 4, 1, 8);
+      }
+#undef TG_TILE
       __syncthreads();
     }
     return;
   }
-  const int total = cs.full;
+  const int total = cs.b256 * NT;
   const int rem = TAIL ? total % (int)gridDim.x : 0;
   const bool tail = rem > 0 && 2 * rem <= (int)gridDim.x;
   const int n_head = tail ? total - rem : total;
@@ -626,7 +615,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_persistent4_kernel(
     };
     auto b_of = [&](int slot, int nt) {
       const size_t b_row0 = (size_t)slot * NW + (SWIGLU ? nt * (BN / 2) : nt * BN);
-      return weight_rsrc(B, slot, NW, b_row0, K);
+      return make_rsrc(B + b_row0 * K, weight_bytes(slot, NW, b_row0, K));
     };
     auto a_of = [&](int row0, int rows) {
       return GATHER ? make_rsrc(A, (uint32_t)A_rows * K * 2)
@@ -1019,27 +1008,32 @@ __global__ __launch_bounds__(256) void grouped_gemm_persistent4_kernel(
         t.row0 += m * (BM / 2);
         t.rows = rows;
         if (rows <= 32)
-          gemm_tile<32, BN / 2, BK, 1, 4, SWIGLU, GATHER, 8>(smem, t, A, B, K, NW, I, C, ldc, perm,
-                                                            1, A_rows);
+          gemm_tile<32, BN / 2, 1, 4, 1, 8, SWIGLU, GATHER>(smem, t, A, B, K, NW, I, C, ldc, perm, 1,
+                                                         A_rows);
         else if (rows <= 64)
-          gemm_tile<64, BN / 2, BK, 2, 2, SWIGLU, GATHER, 6>(smem, t, A, B, K, NW, I, C, ldc, perm,
-                                                            1, A_rows);
+          gemm_tile<64, BN / 2, 2, 2, 1, 6, SWIGLU, GATHER>(smem, t, A, B, K, NW, I, C, ldc, perm, 1,
+                                                         A_rows);
         else
-          gemm_tile<BM / 2, BN / 2, BK, 2, 2, SWIGLU, GATHER, 5>(smem, t, A, B, K, NW, I, C, ldc,
-                                                              perm, 1, A_rows);
+          gemm_tile<BM / 2, BN / 2, 2, 2, 1, 5, SWIGLU, GATHER>(smem, t, A, B, K, NW, I, C, ldc, perm,
+                                                             1, A_rows);
         __syncthreads();
       }
     }
   }
 }
 
-int cu_count() {
+}  // namespace
+
+// One block per CU (a multiple of the XCD count, never 0).
+int gemm_grid() {
   int dev = 0, n = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-    return 256;
-  return n;
+    n = 256;
+  return std::max(kXcds, n / kXcds * kXcds);
 }
+
+namespace {
 
 std::atomic<int> g_tile_policy{kTilesAuto};
 
@@ -1053,7 +1047,7 @@ hipError_t launch_persistent4(const uint16_t* A, const int32_t* offsets, int S, 
   int l = 0;
   while ((1 << l) < kq) ++l;
   const uint32_t m = (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)kq - 1) / (uint64_t)kq);
-  const int grid = std::max(kXcds, cu_count() / kXcds * kXcds);  // a multiple of 8, never 0
+  const int grid = gemm_grid();
   const bool dyn = sched && sched->claims;
   hipLaunchKernelGGL((grouped_gemm_persistent4_kernel<SWIGLU, GATHER, TAIL>), dim3(grid), dim3(256),
                      0, stream, A, offsets, S, B, K, NW, I, C, ldc, NT, perm, kq, m, l, A_rows,

@@ -233,9 +233,10 @@ tg_status ew_forward(const tg_ew_args* a, void* ws, size_t ws_bytes, void* strea
     e = tg::launch_remap_dispatch(ids, a->T, a->k, a->ert, a->E, a->R, a->slot_alive, a->S,
                                   in_place ? nullptr : a->x, a->d, pair_slot, counts, offsets,
                                   L.perm, pair_row, in_place ? nullptr : L.x_perm, n_unserved,
-                                  L.dispatch_ws, s, a->token_valid, L.sched);
+                                  L.dispatch_ws, s, a->token_valid, L.sched,
+                                  {a->d, a->I, tg::gemm_grid()});
   mark(2);
-  // The dispatch has zeroed the GEMMs' dynamic-schedule area.
+  // The dispatch has zeroed the GEMMs' claim counters and planned their tiles.
   tg::GemmSched sched_gu, sched_dn;
   tg::sched_carve(L.sched, &sched_gu, &sched_dn);
   if (e == hipSuccess)
@@ -422,7 +423,8 @@ tg_status tg_ew_replay(const tg_replay_args* a, void* ws, size_t ws_bytes, void*
   hipError_t e = tg::launch_replay_dispatch(
       a->topk_ids, a->T, a->k, a->ert, a->E, a->R, a->slot_alive, a->S, a->pair_slot,
       in_place ? nullptr : a->x, a->d, replay_slot, L.counts, L.offsets, L.perm, L.replay_row,
-      in_place ? nullptr : L.x_perm, n_unserved, n_replayed, L.dispatch_ws, s, L.sched);
+      in_place ? nullptr : L.x_perm, n_unserved, n_replayed, L.dispatch_ws, s, L.sched,
+      {a->d, a->I, tg::gemm_grid()});
   tg::GemmSched sched_gu, sched_dn;
   tg::sched_carve(L.sched, &sched_gu, &sched_dn);
   if (e == hipSuccess)

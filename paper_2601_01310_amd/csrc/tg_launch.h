@@ -19,14 +19,20 @@ tg_status ew_forward(const tg_ew_args* a, void* ws, size_t ws_bytes, void* strea
                      void* const* events);
 tg_status set_error(tg_status s, const char* fmt, ...);
 
-// Work area of the dynamic tile schedule of the two grouped GEMMs of one
-// forward (or replay): per GEMM, 16 claim counters (one per XCD for the
-// tile walk, then one for the pieces of a spilled last round; the rest
-// unused). The dispatch of the same call zeroes the whole area before the
-// GEMMs run.
+// Work area of the two grouped GEMMs of one forward (or replay): per GEMM,
+// 9 claim counters of the dynamic tile schedule (one per XCD for the tile
+// walk, then one for the pieces of a spilled last round), which the dispatch
+// of the same call zeroes before the GEMMs run, and the plan that the
+// dispatch makes: tile shape and row blocks at heights 32, 64, 128 and 256.
 struct GemmSched {
   int32_t* claims;
 };
+constexpr int kSchedPlan = 9;  // words before the plan
+// What the dispatch has to know of the GEMMs to plan them.
+struct GemmDims {
+  int d, I, grid;
+};
+int gemm_grid();
 constexpr size_t kSchedBytes = 2 * 16 * sizeof(int32_t);
 // Carves the two GEMMs' schedules out of a kSchedBytes area (base may be null).
 inline void sched_carve(void* base, GemmSched* gateup, GemmSched* down) {
@@ -53,7 +59,8 @@ hipError_t launch_remap_dispatch(const int32_t* ids, int T, int k, const int32_t
                                  int32_t* pair_slot, int32_t* counts, int32_t* offsets,
                                  int32_t* perm, int32_t* pair_row, uint16_t* x_perm,
                                  int32_t* n_unserved, void* ws, hipStream_t stream,
-                                 const uint8_t* token_valid = nullptr, void* sched_area = nullptr);
+                                 const uint8_t* token_valid = nullptr, void* sched_area = nullptr,
+                                 GemmDims dims = {});
 // Replay batching: pairs whose first-pass slot (prior_slot) is no longer
 // alive, or that had no live candidate, go to their first live candidate now
 // (replay_slot; -1 for every other pair) and are batched by (slot, token,
@@ -64,7 +71,8 @@ hipError_t launch_replay_dispatch(const int32_t* ids, int T, int k, const int32_
                                   const uint16_t* x, int d, int32_t* replay_slot, int32_t* counts,
                                   int32_t* offsets, int32_t* perm, int32_t* replay_row,
                                   uint16_t* x_perm, int32_t* n_unserved, int32_t* n_replayed,
-                                  void* ws, hipStream_t stream, void* sched_area = nullptr);
+                                  void* ws, hipStream_t stream, void* sched_area = nullptr,
+                                  GemmDims dims = {});
 
 // Tile height of the grouped GEMMs: chosen per launch on the device (auto)
 // or forced; every choice gives the same bits.
