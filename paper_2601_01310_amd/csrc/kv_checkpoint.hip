@@ -28,6 +28,11 @@ __device__ __forceinline__ bool seg_ok(uint64_t off, uint64_t bytes, uint64_t li
   return (off % 16 == 0) && (bytes % 16 == 0) && off <= limit && bytes <= limit - off;
 }
 
+// One wave per SIMD and few registers: beside a forward a block of it shares
+// its CU with a block of the grouped GEMM, which leaves 24 registers per lane.
+// (16 waves per block, four segments at a time, copy 4096 segments of 4 KB in
+// 328 us instead of 364, but then the GEMM's block waits for the whole copy:
+// a decode forward beside it takes 757 us instead of 561.)
 __global__ __launch_bounds__(kBlock) void ckpt_copy_kernel(
     const uint4* __restrict__ kv, uint64_t kv_bytes, const uint64_t* __restrict__ seg_off,
     const uint32_t* __restrict__ seg_bytes, int n, uint64_t first_seq, uint4* store,
@@ -99,6 +104,12 @@ __global__ __launch_bounds__(kBlock) void kv_restore_kernel(
   }
 }
 
+// Blocks of a restore: reads of the host's memory go at the link's rate with
+// this many blocks of 4 waves, and at a fraction of it with more of them
+// competing (4096 segments of 4 KB: 445 us with 16 blocks, 297 with 48, 302
+// with 64, 364 with 256, 679 with 1024, 1660 to 1840 with 4096).
+constexpr int kRestoreBlocks = 48;
+
 int grid_for(int n, int max_blocks) { return n < max_blocks ? n : max_blocks; }
 
 }  // namespace
@@ -138,7 +149,7 @@ hipError_t launch_kv_restore(const void* store, size_t store_bytes, const uint64
                              const uint32_t* bytes, int n, void* kv, size_t kv_bytes,
                              uint8_t* status, hipStream_t stream) {
   if (n > 0)
-    hipLaunchKernelGGL(kv_restore_kernel, dim3(grid_for(n, 4096)), dim3(kBlock), 0, stream,
+    hipLaunchKernelGGL(kv_restore_kernel, dim3(grid_for(n, kRestoreBlocks)), dim3(kBlock), 0, stream,
                        static_cast<const uint4*>(store), (uint64_t)store_bytes, commit, seq, src,
                        dst, bytes, n, static_cast<uint4*>(kv), (uint64_t)kv_bytes, status);
   return hipGetLastError();

@@ -184,3 +184,36 @@ def test_strided_checkpoint_on_the_copy_engine_matches_the_oracle():
     assert (status == 1).all()
     want = kv.view(layers * requests, max_len, SEG)[:, pos].reshape(-1)
     assert torch.equal(kv2, want)
+
+
+# More and fewer segments than blocks on both ways, the last round partial.
+@pytest.mark.parametrize("n,max_blocks,seg", [(1, 0, 16), (16, 0, 4096), (17, 0, 1152),
+                                              (63, 0, 8192), (64, 16, 48), (65, 0, 4112),
+                                              (200, 7, 2048), (131, 1, 1024), (49, 64, 4096)])
+def test_segment_counts_around_the_blocks(n, max_blocks, seg):
+    print(f"[gpu] kv blocks n={n} max_blocks={max_blocks} seg={seg}", flush=True)
+    size = (n + 3) * seg
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    kv = torch.randint(0, 256, (size,), dtype=torch.uint8, device=DEV, generator=g)
+    order = np.random.default_rng(n).permutation(n + 3)[:n].astype(np.uint64) * np.uint64(seg)
+    b = np.full(n, seg, dtype=np.uint32)
+    off, nb = (torch.from_numpy(a).to(DEV) for a in (order.view(np.int64), b.view(np.int32)))
+    cap = max(1, n - n // 3)  # the ring keeps the last records
+    store, log = _host(size, fill=0xEE), _host(cap * 3, dtype=torch.int64)
+    commit = _host(1, dtype=torch.int64, fill=0)
+    tg.tg_kv_checkpoint(kv, size, off, nb, n, 11, store, log, cap, commit, max_blocks=max_blocks)
+    torch.cuda.synchronize()
+    e_store, e_log, e_commit = K.checkpoint(kv.cpu().numpy(), np.full(size, 0xEE, dtype=np.uint8),
+                                            np.zeros((cap, 3), dtype=np.uint64), cap, 0, order, b, 11)
+    assert np.array_equal(store.numpy(), e_store)
+    assert np.array_equal(log.numpy().view(np.uint64).reshape(-1, 3), e_log)
+    assert int(commit[0]) == e_commit == 11 + n
+    new = torch.zeros(size, dtype=torch.uint8, device=DEV)
+    status = torch.full((n,), 9, dtype=torch.uint8, device=DEV)
+    seq = torch.arange(11, 11 + n, dtype=torch.int64, device=DEV)
+    tg.tg_kv_restore(store, size, commit, seq, off, off, nb, n, new, size, status)
+    torch.cuda.synchronize()
+    assert (status == 1).all()
+    for o in order.astype(np.int64):
+        assert torch.equal(new[o:o + seg], kv[o:o + seg])
