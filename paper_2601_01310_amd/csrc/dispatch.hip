@@ -12,8 +12,10 @@
 //   2. scan: per-slot totals, exclusive slot offsets, and the position of
 //      every (chunk, slot) within its slot in chunk order (the histograms
 //      are slot-major, so one wave scans one slot's chunks). When S times
-//      the number of chunks is at most 1024, each scatter block does this
-//      for itself from the whole histogram instead, and the launch is saved;
+//      the number of chunks is at most 16384, each scatter block does this
+//      for itself from the whole histogram instead, and the launch is saved
+//      (40 slots x 256 chunks: 13.9 us in two kernels, 8.5 in one; x 63
+//      chunks 9.6 and 6.2);
 //   3. scatter: each wave walks an equal share of a chunk in pair order and
 //      ranks the pairs of each group of 64 by slot: one ballot per bit of
 //      the slot index gives every lane the lanes that share its slot, so the
@@ -34,7 +36,7 @@ namespace {
 
 constexpr int kMaxS = 1024;
 constexpr int kBlock = 256;
-constexpr int kFusedScanHist = 1024;  // S * nchunks up to which scatter scans by itself
+constexpr int kFusedScanHist = 16384;  // S * nchunks up to which scatter scans by itself
 
 // Slot of a pair of expert e: the first live ERT candidate of e.
 // REPLAY: -1 also when the first pass's slot pr is still alive (its result
@@ -255,31 +257,37 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(
   __shared__ int base[SCAN ? kMaxS : 1];  // first row of this chunk's pairs on each slot
   __shared__ int tot[SCAN ? kMaxS : 1];
   __shared__ int wsum[kWaves];
-  for (int i = threadIdx.x; i < kWaves * kMaxS; i += kBlock) (&cnt[0][0])[i] = 0;
-  constexpr int kPer = SCAN ? kFusedScanHist / kBlock : 1;
-  int hv[kPer];
+  for (int s = lane; s < S; s += kWave) cnt[wave][s] = 0;
   if (SCAN) {
-    // Thread i loads histogram entries i, i + 256, ... (all loads at once),
-    // and the slot totals and this chunk's positions are summed in LDS
-    // (integer atomics: the sums do not depend on their order).
-    const int nh = S * nchunks;
+    // Wave w takes slots w, w + 4, ..., kGroup of them at a time so that their
+    // loads are in flight together: lane l holds chunks l, l + 64, ... of each;
+    // the sums over all chunks and over the chunks before this one are DPP
+    // reductions.
+    constexpr int kGroup = 4, kPer = kDispatchChunks / kWave;
+    for (int s0 = wave; s0 < S; s0 += kGroup * kWaves) {
+      int v[kGroup][kPer];
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const int j = threadIdx.x + q * kBlock;
-      hv[q] = j < nh ? hist[j] : 0;
-    }
-    for (int s = threadIdx.x; s < S; s += kBlock) {
-      tot[s] = 0;
-      base[s] = 0;
-    }
-    __syncthreads();
+      for (int g = 0; g < kGroup; ++g)
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const int j = threadIdx.x + q * kBlock;
-      if (hv[q]) {
-        const int s = j / nchunks, c = j - s * nchunks;
-        atomicAdd(&tot[s], hv[q]);
-        if (c < (int)blockIdx.x) atomicAdd(&base[s], hv[q]);
+        for (int q = 0; q < kPer; ++q) {
+          const int s = s0 + g * kWaves, c = lane + q * kWave;
+          v[g][q] = s < S && c < nchunks ? hist[(size_t)s * nchunks + c] : 0;
+        }
+#pragma unroll
+      for (int g = 0; g < kGroup; ++g) {
+        const int s = s0 + g * kWaves;
+        int all = 0, before = 0;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+          all += v[g][q];
+          before += lane + q * kWave < (int)blockIdx.x ? v[g][q] : 0;
+        }
+        all = wave_reduce<false>(all);
+        before = wave_reduce<false>(before);
+        if (lane == 0 && s < S) {
+          tot[s] = all;
+          base[s] = before;
+        }
       }
     }
   }
@@ -374,7 +382,10 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(
 // same_slot_lanes (one LDS add per distinct slot), a wave scan with one
 // barrier gives the slot offsets, and the pairs are then ranked 1024 at a
 // time in pair order (wave w holds pairs 64w .. 64w+63 of the group) exactly
-// as scatter_kernel does, so rows follow (slot, token, rank).
+// as scatter_kernel does, so rows follow (slot, token, rank). With a schedule
+// area a second block counts the pairs too and plans the GEMMs, beside the
+// first one's ranking (planned by two waves of the same block, the kernel took
+// 1.5 us more).
 constexpr int kOneBlock = 1024;
 constexpr int kSmallPairs = 4096;
 constexpr int kSmallPer = kSmallPairs / kOneBlock;
@@ -393,7 +404,6 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
   // their first row; 0 wherever wave w has no pair on s.
   __shared__ int cnt[kWaves][kMaxS];
   __shared__ int run[kMaxS];
-  __shared__ int tot[kMaxS];  // pairs of each slot
   __shared__ int ert_s[kMaxErt];
   __shared__ uint8_t alive_s[kMaxS];
   __shared__ int wsum[kWaves];
@@ -459,6 +469,11 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
   }
   __syncthreads();
 
+  if (blockIdx.x == 1) {  // the planner
+    plan_gemms(wave, S, [&](int s) { return run[s]; }, sched, dims);
+    return;
+  }
+
   // Exclusive scan of the slot totals: a wave scan per 64 slots, then the
   // totals of the waves before.
   const int total = (tid < S) ? run[tid] : 0;
@@ -471,10 +486,7 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
   if (lane == kWave - 1) wsum[wave] = incl;
   __syncthreads();
   for (int w = 0; w < wave; ++w) incl += wsum[w];
-  if (tid < S) {
-    run[tid] = incl - total;  // next row of the slot
-    tot[tid] = total;
-  }
+  if (tid < S) run[tid] = incl - total;  // next row of the slot
 
   int my_row[kSmallPer];
 #pragma unroll
@@ -525,14 +537,7 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
       if (my_row[i] >= 0) perm[my_row[i]] = p;
     }
   }
-  if (sched) {
-    zero_claims(sched, tid);
-    // The last two waves, which have the fewest pairs, plan the GEMMs. (The
-    // totals were written before the barriers of the first ranked group; a
-    // batch without pairs has none.)
-    if (npairs == 0) __syncthreads();
-    plan_gemms(kWaves - 1 - wave, S, [&](int s) { return tot[s]; }, sched, dims);
-  }
+  if (sched) zero_claims(sched, tid);
 }
 
 __global__ __launch_bounds__(kBlock) void gather_kernel(const uint4* __restrict__ x,
@@ -583,11 +588,11 @@ hipError_t remap_dispatch(bool replay, const int32_t* ids, int T, int k, const i
   const int sbits = (S > 1) ? 32 - __builtin_clz((unsigned)(S - 1)) : 0;
   if (npairs <= kSmallPairs) {
     if (replay)
-      hipLaunchKernelGGL(dispatch_one_block_kernel<true>, dim3(1), dim3(kOneBlock), 0, stream, ids,
+      hipLaunchKernelGGL(dispatch_one_block_kernel<true>, dim3(sched ? 2 : 1), dim3(kOneBlock), 0, stream, ids,
                          npairs, k, ert, E, R, alive, S, sbits, nullptr, prior, pair_slot, counts,
                          offsets, perm, pair_row, n_unserved, total_out, sched, dims);
     else
-      hipLaunchKernelGGL(dispatch_one_block_kernel<false>, dim3(1), dim3(kOneBlock), 0, stream,
+      hipLaunchKernelGGL(dispatch_one_block_kernel<false>, dim3(sched ? 2 : 1), dim3(kOneBlock), 0, stream,
                          ids, npairs, k, ert, E, R, alive, S, sbits, token_valid, nullptr,
                          pair_slot, counts, offsets, perm, pair_row, n_unserved, total_out, sched,
                          dims);
