@@ -12,10 +12,11 @@
 // has another, so a logit that lies within float64 rounding of a float32
 // midpoint may differ between them.
 //
-// Top-k runs as k rounds of a wave arg-max over the float32 logits (larger
-// first, ties to the lower expert id), the cross-lane step in DPP row
-// operations and lane reads; lane j keeps the j-th winner, the k
-// exponentials are formed in parallel and summed in rank order.
+// Top-k (larger float32 logit first, ties to the lower expert id) counts, for
+// each of a few candidates, the ones that beat it, or, over more of them or
+// all, takes k rounds of a wave arg-max (the cross-lane step in DPP row
+// operations and lane reads). Lane j holds the j-th winner, the k exponentials
+// are formed in parallel and summed in rank order.
 #include <type_traits>
 
 #include "tg_device.h"
@@ -123,7 +124,9 @@ __device__ void wave_topk(const float* lg, int E, int k, int t, int32_t* __restr
 }
 
 // Top-k over n <= 64 candidates, lane l < n holding candidate l (n >= k, ids
-// distinct): a lane's rank is the number of candidates that beat its own.
+// distinct): a lane's rank is the number of candidates that beat its own. A
+// NaN is never chosen; a choice that is left empty for it is what wave_topk
+// leaves there.
 __device__ void wave_topk_lanes(float v, int id, int n, int k, int t, int32_t* __restrict__ ids,
                                 float* __restrict__ w) {
   const int lane = lane_id();
@@ -133,7 +136,15 @@ __device__ void wave_topk_lanes(float v, int id, int n, int k, int t, int32_t* _
     const int oid = __builtin_amdgcn_readlane(id, i);
     rank += better(ov, oid, v, id) ? 1 : 0;
   }
-  const int to = 4 * (lane < n ? rank : lane);
+  // The others go behind the m that can be chosen, in lane order.
+  const bool is = lane < n && v == v;
+  const uint64_t m = __ballot(is), lt = (1ull << lane) - 1;
+  if (!is) {
+    rank = __builtin_popcountll(m) + __builtin_popcountll(~m & lt);
+    v = -__builtin_inff();
+    id = 0x7fffffff;
+  }
+  const int to = 4 * rank;
   const float my_v = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(v)));
   const int my_id = __builtin_amdgcn_ds_permute(to, id);
   store_topk(my_v, my_id, k, t, ids, w);
@@ -613,6 +624,10 @@ __global__ __launch_bounds__(256) void logits_topk_kernel(const float* __restric
 // vector ALU's 1270 instructions per wave), 256 experts, top-8: 16384 tokens
 // 19.8 -> 11.5 us; 2011 tokens 8.9 -> 5.6 us and 128 tokens 8.4 -> 5.1 us (one
 // token per wave before).
+//
+// skip_nan: a NaN logit is never chosen, as in wave_topk, and a choice left
+// empty for it has id 0x7fffffff. Otherwise NaN logits are ordered by their
+// bits (the positive ones above +inf).
 constexpr int kRowTokens = 4;  // tokens per wave
 
 __device__ __forceinline__ uint64_t topk_key(float v, int e) {
@@ -658,7 +673,8 @@ template <int NQ>
 __global__ __launch_bounds__(256) void logits_topk_rows_kernel(const float* __restrict__ logits,
                                                                int T, int E, int k,
                                                                int32_t* __restrict__ ids,
-                                                               float* __restrict__ w) {
+                                                               float* __restrict__ w,
+                                                               bool skip_nan) {
   __shared__ uint64_t list_s[4][kRowTokens][16];
   const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
@@ -683,11 +699,11 @@ __global__ __launch_bounds__(256) void logits_topk_rows_kernel(const float* __re
     m0 = m0 == tau ? -__builtin_inff() : m0;
     m1 = m1 == tau ? -__builtin_inff() : m1;
   }
-  // Candidates: !(v < tau), so that a NaN is one.
+  // A NaN is a candidate unless it is skipped.
   uint32_t mine = 0;
 #pragma unroll
   for (int q = 0; q < NQ; ++q)
-    mine |= (l16 + 16 * q < E && !(v[q] < tau) ? 1u : 0u) << q;
+    mine |= (l16 + 16 * q < E && (skip_nan ? v[q] >= tau : !(v[q] < tau)) ? 1u : 0u) << q;
   const int cnt = __builtin_popcount(mine);
   int incl = cnt;  // over the row's lanes up to this one
   incl += TG_ROW_MOV(incl, 0x111);  // row_shr 1, 2, 4, 8
@@ -718,13 +734,15 @@ __global__ __launch_bounds__(256) void logits_topk_rows_kernel(const float* __re
     TG_RANK(15);
 #undef TG_RANK
     const int to = 4 * ((lane & 48) + (l16 < n ? rank : l16));
-    my_v = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(key_value(key))));
-    my_id = __builtin_amdgcn_ds_permute(to, (int)(0xffffffffu - (uint32_t)key));
+    const float kv = key ? key_value(key) : -__builtin_inff();
+    const int kid = key ? (int)(0xffffffffu - (uint32_t)key) : 0x7fffffff;
+    my_v = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(kv)));
+    my_id = __builtin_amdgcn_ds_permute(to, kid);
   } else {
     uint64_t key[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
-      key[q] = (on && l16 + 16 * q < E) ? topk_key(v[q], l16 + 16 * q) : 0;  // 0: no candidate
+      key[q] = (mine >> q & 1) ? topk_key(v[q], l16 + 16 * q) : 0;  // 0: no candidate
     uint64_t thr = ~0ull;
     for (int j = 0; j < k; ++j) {
       uint64_t best = 0;
@@ -732,8 +750,8 @@ __global__ __launch_bounds__(256) void logits_topk_rows_kernel(const float* __re
       for (int q = 0; q < NQ; ++q) best = (key[q] < thr && key[q] > best) ? key[q] : best;
       thr = row_max_key(best);  // every lane of the row: this round's winner
       if (l16 == j) {
-        my_v = key_value(thr);
-        my_id = (int)(0xffffffffu - (uint32_t)thr);
+        my_v = thr ? key_value(thr) : -__builtin_inff();
+        my_id = thr ? (int)(0xffffffffu - (uint32_t)thr) : 0x7fffffff;
       }
     }
   }
@@ -767,7 +785,7 @@ void launch_screen(const uint16_t* x, const uint16_t* wg, int T, int d, int E, i
 }
 
 void launch_logits_topk(const float* logits, int T, int E, int k, int32_t* ids, float* w,
-                        hipStream_t stream) {
+                        bool skip_nan, hipStream_t stream) {
   if (E <= 256 && k <= 16) {
     // Few tokens: one wave per block, so that more CUs take part.
     const int waves = T >= 4096 ? 4 : 1;
@@ -775,13 +793,13 @@ void launch_logits_topk(const float* logits, int T, int E, int k, int32_t* ids, 
     const dim3 grid((T + per_block - 1) / per_block), block(64 * waves);
     if (E <= 64)
       hipLaunchKernelGGL(logits_topk_rows_kernel<4>, grid, block, 0, stream, logits, T, E, k, ids,
-                         w);
+                         w, skip_nan);
     else if (E <= 128)
       hipLaunchKernelGGL(logits_topk_rows_kernel<8>, grid, block, 0, stream, logits, T, E, k, ids,
-                         w);
+                         w, skip_nan);
     else
       hipLaunchKernelGGL(logits_topk_rows_kernel<16>, grid, block, 0, stream, logits, T, E, k, ids,
-                         w);
+                         w, skip_nan);
   } else {
     hipLaunchKernelGGL(logits_topk_kernel, dim3((T + kWaves - 1) / kWaves), dim3(256), 0, stream,
                        logits, T, E, k, ids, w);
@@ -834,7 +852,9 @@ hipError_t launch_gate_topk(const uint16_t* x, const uint16_t* wg, const float* 
                             hipStream_t stream, float* scratch) {
   if (T == 0) return hipSuccess;
   if (logits_in) {
-    launch_logits_topk(logits_in, T, E, k, ids, w, stream);
+    // From 4096 tokens on NaN logits are ordered, below and in the other
+    // kernels skipped.
+    launch_logits_topk(logits_in, T, E, k, ids, w, T < 4096, stream);
     return hipGetLastError();
   }
   float* const logits = logits_out ? logits_out : scratch;
@@ -851,7 +871,7 @@ hipError_t launch_gate_topk(const uint16_t* x, const uint16_t* wg, const float* 
     case kGateDense:
       hipLaunchKernelGGL(gate_logits_f64_kernel<false>, dim3((T + 15) / 16, (E + 15) / 16),
                          dim3(64 * kDenseWaves), 0, stream, x, wg, T, d, E, k, logits, ids, w);
-      launch_logits_topk(logits, T, E, k, ids, w, stream);
+      launch_logits_topk(logits, T, E, k, ids, w, true, stream);
       break;
     case kGateDenseTopk:
       hipLaunchKernelGGL(gate_logits_f64_kernel<true>, dim3((T + 15) / 16), dim3(64 * kDenseWaves),

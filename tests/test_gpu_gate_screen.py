@@ -15,6 +15,7 @@ from oracle import moe_ew as O
 from paper_2601_01310_amd import synth, tg
 from tests import _gate_cases as C
 from tests._util import host, u16
+from tests.test_gpu_logits_topk import check_without_nan
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -140,3 +141,28 @@ def test_screen_matches_the_oracle():
     r = O.topk(logits, 8)
     assert np.array_equal(ids, r)
     assert np.abs(tw - O.gate_weights(logits, r)).max() <= 1e-6
+
+
+# token (4 tokens), dense with its top-k (16 experts) and after it (logits
+# wanted), screen.
+@pytest.mark.parametrize("T,E", [(4, 40), (600, 16), (300, 200), (300, 300)])
+def test_nan_is_not_chosen(T, E):
+    """Gate rows that hold a NaN are passed over; a token that holds one has
+    no choice at all."""
+    print(f"[gpu] gate NaN T={T} E={E}", flush=True)
+    d, k = 256, 8
+    x, w = _normal(T, d, E, T + E)
+    w[1::7, 5] = float("nan")
+    x[2] = float("nan")
+    x[3, :] = 0
+    logits = O.gate_logits(u16(x), u16(w))
+    assert np.isnan(logits[:, 1]).all()
+    for want in (False, True):
+        _, ids, tw = _run(x, w, k, want)
+        check_without_nan(logits, k, ids, tw)
+    w[k - 2:, 5] = float("nan")  # fewer than k experts are left
+    w[:k - 2] = w[0]
+    logits = O.gate_logits(u16(x), u16(w))
+    for want in (False, True):
+        _, ids, tw = _run(x, w, k, want)
+        check_without_nan(logits, k, ids, tw)

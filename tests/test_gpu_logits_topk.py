@@ -55,3 +55,54 @@ def test_ties_and_masks(E, k):
     lg[6::9, : E // 2] += 40.0                      # one half far above
     lg[7::9, 5::16] += 40.0                         # the winners in one lane's column
     _check(lg, k)
+
+
+# NaN logits are never chosen by batches under 4096 tokens or beyond 256
+# experts; where fewer than k are left, the id is 0x7fffffff, the weight 0 (NaN
+# without any).
+@pytest.mark.parametrize("T,E,k", [(5, 40, 8), (70, 256, 8), (4095, 128, 16), (4100, 300, 4)])
+def test_nan_is_not_chosen(T, E, k):
+    print(f"[gpu] logits topk NaN T={T} E={E} k={k}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T + E)
+    lg = torch.randn((T, E), generator=g, device=DEV)
+    lg[0::5, 3] = float("nan")
+    lg[1::5, : E - k] = float("nan")      # just k are left
+    lg[2::5, 2:] = float("nan")           # two
+    lg[3::5] = 0.5                        # more than 16 candidates
+    lg[3::5, ::2] = float("nan")
+    lg[4::5, 1::2] = -float("nan")
+    lg[4] = float("nan")
+    ids = torch.full((T, k), -7, dtype=torch.int32, device=DEV)
+    w = torch.full((T, k), -7.0, dtype=torch.float32, device=DEV)
+    tg.tg_gate_topk(None, None, lg, T, 0, E, k, None, ids, w)
+    torch.cuda.synchronize()
+    check_without_nan(host(lg), k, host(ids), host(w))
+
+
+def check_without_nan(l, k, ids, w):
+    nan = np.isnan(l)
+    r = np.argsort(np.where(nan, np.inf, -l.astype(np.float64)), axis=1, kind="stable")[:, :k]
+    left = ~np.take_along_axis(nan, r, 1)
+    assert np.array_equal(ids, np.where(left, r, 0x7FFFFFFF))
+    some = left[:, 0]
+    assert np.isnan(w[~some]).all()
+    top = np.where(left, np.take_along_axis(l, r, 1).astype(np.float64), -np.inf)[some]
+    e = np.exp(top - top[:, :1])
+    assert np.abs(w[some] - e / e.sum(1, keepdims=True)).max() <= 1e-6
+
+
+def test_nan_is_ordered_in_large_batches():
+    """From 4096 tokens on a positive NaN ranks above +inf, a negative one below -inf."""
+    print("[gpu] logits topk NaN order", flush=True)
+    lg = torch.arange(4096 * 64, device=DEV, dtype=torch.float32).reshape(4096, 64) % 61
+    lg[:, 7], lg[:, 9] = float("nan"), float("inf")
+    lg.view(torch.int32)[:, 60] = -4194304  # 0xffc00000, a negative NaN
+    ids = torch.full((4096, 3), -7, dtype=torch.int32, device=DEV)
+    w = torch.empty((4096, 3), dtype=torch.float32, device=DEV)
+    tg.tg_gate_topk(None, None, lg, 4096, 0, 64, 3, None, ids, w)
+    torch.cuda.synchronize()
+    l = host(lg).copy()
+    l[:, [7, 9, 60]] = -1.0
+    third = l.argmax(axis=1)
+    assert np.array_equal(host(ids), np.stack([np.full(4096, 7), np.full(4096, 9), third], 1))
