@@ -102,14 +102,19 @@ __device__ __forceinline__ uint64_t same_slot_lanes(int s, int sbits) {
 
 // Plans both GEMMs of the call (wave 0 the gate/up GEMM, wave 1 the down
 // GEMM; other waves have nothing to do here). count(s): rows of slot s.
-template <typename Count>
+// COUNTS false leaves the plan's row blocks to the caller.
+template <bool COUNTS, typename Count>
 __device__ __forceinline__ void plan_gemms(int which, int S, Count count, int32_t* sched,
                                            const GemmDims& g) {
   if (which > 1) return;
   const Census cs = census(S, count);
   const int shape = which == 0 ? choose_shape<true, false>(cs, g.grid, g.d, g.I)
                                : choose_shape<false, true>(cs, g.grid, g.I, g.d);
-  store_plan(sched + 16 * which, cs, shape);
+  int32_t* const plan = sched + 16 * which + kSchedPlan;
+  const int lane = lane_id();
+  if (lane == 0) plan[0] = shape;
+  if (COUNTS && lane < 4)
+    plan[1 + lane] = lane == 0 ? cs.b32 : lane == 1 ? cs.b64 : lane == 2 ? cs.b128 : cs.b256;
 }
 
 // The claim counters of both GEMMs start at zero.
@@ -245,7 +250,7 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(
   const int lane = lane_id();
   const bool planner = (int)blockIdx.x == nchunks;
   if (!SCAN && planner) {
-    plan_gemms(wave, S, [&](int s) { return offsets[s + 1] - offsets[s]; }, sched, dims);
+    plan_gemms<true>(wave, S, [&](int s) { return offsets[s + 1] - offsets[s]; }, sched, dims);
     return;
   }
   // The chunk's pairs are split evenly (in multiples of 64) over the waves.
@@ -293,7 +298,7 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(
   }
   __syncthreads();
   if (SCAN && planner) {
-    plan_gemms(wave, S, [&](int s) { return tot[s]; }, sched, dims);
+    plan_gemms<true>(wave, S, [&](int s) { return tot[s]; }, sched, dims);
     return;
   }
   if (SCAN) {
@@ -383,9 +388,12 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(
 // barrier gives the slot offsets, and the pairs are then ranked 1024 at a
 // time in pair order (wave w holds pairs 64w .. 64w+63 of the group) exactly
 // as scatter_kernel does, so rows follow (slot, token, rank). With a schedule
-// area a second block counts the pairs too and plans the GEMMs, beside the
-// first one's ranking (planned by two waves of the same block, the kernel took
-// 1.5 us more).
+// area a second block counts the pairs too and chooses the GEMMs' tile shapes,
+// beside the first one's ranking (chosen by two waves of the same block, the
+// kernel took 1.5 us more). That block reads the liveness mask again, which may
+// have been written meanwhile: its choice, right for any rows, is all that is
+// taken from it, and the row blocks that the GEMMs walk are counted by the
+// first block from the totals that become the offsets.
 constexpr int kOneBlock = 1024;
 constexpr int kSmallPairs = 4096;
 constexpr int kSmallPer = kSmallPairs / kOneBlock;
@@ -407,6 +415,7 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
   __shared__ int ert_s[kMaxErt];
   __shared__ uint8_t alive_s[kMaxS];
   __shared__ int wsum[kWaves];
+  __shared__ int blocks[4];  // row blocks at heights 32, 64, 128 and 256
   __shared__ int nu;
   const int tid = threadIdx.x;
   const int wave = tid / kWave, lane = lane_id();
@@ -438,6 +447,7 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
   }
   for (int j = tid; j < kWaves * S; j += kOneBlock) cnt[j / S][j % S] = 0;
   if (tid == 0) nu = 0;
+  if (tid < 4) blocks[tid] = 0;
   __syncthreads();
 
   // Global stores wait until the end: on this chip a wait for a load also
@@ -470,7 +480,7 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
   __syncthreads();
 
   if (blockIdx.x == 1) {  // the planner
-    plan_gemms(wave, S, [&](int s) { return run[s]; }, sched, dims);
+    plan_gemms<false>(wave, S, [&](int s) { return run[s]; }, sched, dims);
     return;
   }
 
@@ -484,6 +494,13 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
     if (lane >= off) incl += t;
   }
   if (lane == kWave - 1) wsum[wave] = incl;
+  if (sched && wave * kWave < S) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const int n = wave_reduce<false>((total + (32 << h) - 1) / (32 << h));
+      if (lane == 0) atomicAdd(&blocks[h], n);
+    }
+  }
   __syncthreads();
   for (int w = 0; w < wave; ++w) incl += wsum[w];
   if (tid < S) run[tid] = incl - total;  // next row of the slot
@@ -537,7 +554,10 @@ __global__ __launch_bounds__(kOneBlock) void dispatch_one_block_kernel(
       if (my_row[i] >= 0) perm[my_row[i]] = p;
     }
   }
-  if (sched) zero_claims(sched, tid);
+  if (sched) {
+    zero_claims(sched, tid);
+    if (tid < 8) sched[tid / 4 * 16 + kSchedPlan + 1 + tid % 4] = blocks[tid % 4];
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void gather_kernel(const uint4* __restrict__ x,

@@ -153,12 +153,4 @@ __device__ __forceinline__ Shape choose_shape(const Census& cs, int G, int K, in
   return (Shape)__builtin_amdgcn_readfirstlane(take ? best : small ? (int)k32 : (int)k256);
 }
 
-// The plan of one GEMM in its schedule area: GemmSched's kPlan words.
-__device__ __forceinline__ void store_plan(int32_t* claims, const Census& cs, int shape) {
-  const int lane = lane_id();
-  const int v = lane == 0 ? shape : lane == 1 ? cs.b32 : lane == 2 ? cs.b64
-              : lane == 3 ? cs.b128 : cs.b256;
-  if (lane < 5) claims[kSchedPlan + lane] = v;
-}
-
 }  // namespace tg
