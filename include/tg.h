@@ -67,7 +67,9 @@ const char* tg_last_error(void);
  * equal logits ordered by lower expert id. topk_w[t,j] =
  * exp(l_j - l_0) / sum_{j'<k} exp(l_j' - l_0) in float32, which equals the
  * softmax over all E renormalised over the chosen k. logits_out [T,E] is
- * written when non-NULL. Logits must be finite.
+ * written when non-NULL. Logits must be finite. The products of a logit are
+ * added in one order whatever T and E are, so a token's results do not depend
+ * on the batch it is in.
  */
 tg_status tg_gate_topk(const uint16_t* x, const uint16_t* w_gate, const float* logits_in,
                        int T, int d, int E, int k,

@@ -8,9 +8,10 @@
 //           them (logits wanted, or memory for them at hand);
 //   screen  bf16 MFMA sums with an error bound tell which experts can be
 //           among the k largest; only those get a float64 logit.
-// The float64 sums of the first and the last run in the same order; dense
-// has another, so a logit that lies within float64 rounding of a float32
-// midpoint may differ between them.
+// All three add in one order, so that a token's ids and weights do not depend
+// on the batch it is in: 64 partial sums, the l-th over the 8-element chunks
+// l, l + 64, ... of the row, element by element; then neighbours are added
+// pairwise up to sixteen partial sums, and the four sixteens in order.
 //
 // Top-k (larger float32 logit first, ties to the lower expert id) counts, for
 // each of a few candidates, the ones that beat it, or, over more of them or
@@ -526,16 +527,43 @@ __global__ __launch_bounds__(64 * NW) void gate_token_topk_kernel(
   if (wave == 0) wave_topk_any(lg, E, k, t, ids, w);
 }
 
+// Four chunks of 8 elements, one per 16-lane row of the wave (row q holds chunk
+// q of its lane's token or expert), turned over: out[m] on row q gets elements
+// q (low half) and 4 + q (high half) of chunk m.
+__device__ __forceinline__ void turn_chunks(const uint4& v, uint32_t* out) {
+  // Word j: elements j and 4 + j of the lane's own chunk. Then the 4 x 4 blocks
+  // of (word, row) are transposed: rows 2, 3 of words 0, 1 against rows 0, 1 of
+  // words 2, 3, then odd rows of even words against even rows of odd ones.
+  const uint32_t w0 = __builtin_amdgcn_perm(v.z, v.x, 0x05040100);
+  const uint32_t w1 = __builtin_amdgcn_perm(v.z, v.x, 0x07060302);
+  const uint32_t w2 = __builtin_amdgcn_perm(v.w, v.y, 0x05040100);
+  const uint32_t w3 = __builtin_amdgcn_perm(v.w, v.y, 0x07060302);
+  const auto a = __builtin_amdgcn_permlane32_swap(w0, w2, false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(w1, w3, false, false);
+  const auto lo = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  out[0] = lo[0];
+  out[1] = lo[1];
+  out[2] = hi[0];
+  out[3] = hi[1];
+}
+
 // All logits [T, E] in float64 on the matrix cores (v_mfma_f64_16x16x4: the
 // rate of the vector unit's float64 FMA, but the operands are widened once
 // per 16 tokens or experts instead of once per product, beside it). A block
-// of 16 waves forms 16 tokens x 16 experts, each wave over every 16th
-// 32-element piece of the hidden dimension (the split keeps few tokens from
-// being one long chain; wider tiles with fewer waves measured 5 % faster at
-// 4096 tokens of 256 experts and half as fast at 128); the parts are added
-// in LDS in a fixed order and the float64 sum is rounded once. Lane l holds
-// row l % 16, elements 8 (l / 16) .. + 7 of a piece; step j multiplies
-// element j of every lane. 4096 x 256 x 7168: 282 us, 53 TFLOP/s of float64.
+// of 16 waves forms 16 tokens x 16 experts. The instruction adds its four
+// products to the accumulator one after the other, each rounded as an FMA
+// (checked on an MI355X: 2^20 sums, none different), so chains of it give the
+// partial sums of logits_of bit for bit: wave w holds partial sums 4 w .. + 3 in
+// four accumulators, takes the 32-element pieces w, w + 16, ... (four chunks)
+// and feeds chunk m to accumulator m, elements 0-3 and then 4-7. Lane l loads
+// chunk l / 16 of row l % 16 and gets element l / 16 of each half of all four
+// chunks by turn_chunks. The waves' sums are added in LDS in the order of
+// wave_sum_f64 and rounded once. 4096 x 256 x 7168: 310 us, 48 TFLOP/s of
+// float64 (280 us with one accumulator per wave and no turning, in an order of
+// its own; the float64 MFMA does not overlap the vector unit's work). Wider
+// tiles with fewer waves measured 5 % faster there and half as fast at 128
+// tokens.
 // TOPK (E <= 16): the block holds all logits of its tokens and finishes them,
 // one wave each; logits may then be null.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -545,7 +573,7 @@ __global__ __launch_bounds__(64 * kDenseWaves) void gate_logits_f64_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int T, int d, int E, int k,
     float* __restrict__ logits, int32_t* __restrict__ ids, float* __restrict__ w) {
   __shared__ float lg[TOPK ? 16 : 1][16];
-  __shared__ f64x4 part[kDenseWaves - 1][kWave];
+  __shared__ f64x4 part[kDenseWaves][kWave];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = lane_id();
   const int t0 = blockIdx.x * 16, e0 = blockIdx.y * 16;
@@ -553,11 +581,12 @@ __global__ __launch_bounds__(64 * kDenseWaves) void gate_logits_f64_kernel(
   const uint16_t* const xr = x + (size_t)min(t0 + (lane & 15), T - 1) * d + 8 * (lane / 16);
   const uint16_t* const wr = wg + (size_t)min(e0 + (lane & 15), E - 1) * d + 8 * (lane / 16);
   const int np = d / 32;
-  auto widen = [](const uint4& v, int j) {
-    const uint32_t u = (j >> 1) == 0 ? v.x : (j >> 1) == 1 ? v.y : (j >> 1) == 2 ? v.z : v.w;
-    return (double)__uint_as_float((j & 1) ? u & 0xffff0000u : u << 16);
+  auto widen = [](uint32_t u, int half) {
+    return (double)__uint_as_float(half ? u & 0xffff0000u : u << 16);
   };
-  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  f64x4 acc[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
   uint4 xn, wn;
   auto load = [&](int p) {
     p = min(p, np - 1);
@@ -566,23 +595,31 @@ __global__ __launch_bounds__(64 * kDenseWaves) void gate_logits_f64_kernel(
   };
   load(wave);
   for (int p = wave; p < np; p += kDenseWaves) {
-    const uint4 xv = xn, wv = wn;
+    uint32_t xv[4], wv[4];
+    turn_chunks(xn, xv);
+    turn_chunks(wn, wv);
     load(p + kDenseWaves);
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(widen(xv, j), widen(wv, j), acc, 0, 0, 0);
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(widen(xv[m], half), widen(wv[m], half),
+                                                      acc[m], 0, 0, 0);
   }
-  if (wave > 0) part[wave - 1][lane] = acc;
+  part[wave][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   __syncthreads();
   if (wave == 0) {
-    for (int q = 0; q < kDenseWaves - 1; ++q) acc += part[q][lane];
+    f64x4 sum = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < kDenseWaves; q += 4)
+      sum += (part[q][lane] + part[q + 1][lane]) + (part[q + 2][lane] + part[q + 3][lane]);
     // Register r of lane l: token 4 r + l / 16, expert l % 16.
     const int e = e0 + (lane & 15);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int t = t0 + 4 * r + lane / 16;
-      if (TOPK) lg[4 * r + lane / 16][lane & 15] = (float)acc[r];
-      if (t < T && e < E && (!TOPK || logits)) logits[(size_t)t * E + e] = (float)acc[r];
+      if (TOPK) lg[4 * r + lane / 16][lane & 15] = (float)sum[r];
+      if (t < T && e < E && (!TOPK || logits)) logits[(size_t)t * E + e] = (float)sum[r];
     }
   }
   if (TOPK) {
@@ -808,23 +845,23 @@ void launch_logits_topk(const float* logits, int T, int E, int k, int32_t* ids, 
 
 // Which kernel forms the logits in weight mode. `stored`: there is memory for
 // all T x E logits (the caller wants them, or has scratch to lend). Measured,
-// us, back-to-back calls of tg_gate_topk, whose host side alone takes about
-// 8 us (dense counts its second launch, the top-k, from E = 17 on; `before`:
-// one token per wave, the gate matrix in LDS where it fits, else from L2):
+// us, calls of tg_gate_topk back to back (dense counts its second launch, the
+// top-k, from E = 17 on; `before`: one token per wave, the gate matrix in LDS
+// where it fits, else from L2):
 //   d, E, k       T =            1    128    512   1024   2048   4096
-//   7168, 256, 8  token         58     58      -      -      -      -
-//                 dense         27     30     47     79    146    282
-//                 screen        71     96    100    101    101    105
+//   7168, 256, 8  token         54     56      -      -      -      -
+//                 dense         26     29     47     84    159    310
+//                 screen        71     96     99    101    101    102
 //                 before      1073   1177   1184   1212   1185   1334
 //   4096, 64, 6   token         12     13      -      -      -      -
-//                 dense         16     17     18     19     28     46
-//                 screen        19     30     31     31     32     34
+//                 dense         16     17     17     17     29     51
+//                 screen        19     30     31     31     32     32
 //                 before        94    116    111    178    176    187
 //   7168, 16, 8   token          -      -     18     32      -      -
-//                 dense          -      -     27     27     27     27
+//                 dense          -      -     28     28     29     30
 //                 before         -      -     51     79     79     88
-//   4096, 8, 2    token        8.6    8.6    8.6     10      -      -
-//                 dense          -      -     15     15     15     16
+//   4096, 8, 2    token        4.6    5.0    6.6    9.3      -      -
+//                 dense          -      -     16     16     17     17
 //                 screen        13     17     18     18     19     21
 //                 before       9.8     17     17     18     18     19
 enum GateKernel { kGateToken, kGateDense, kGateDenseTopk, kGateScreen };

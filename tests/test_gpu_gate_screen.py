@@ -143,6 +143,62 @@ def test_screen_matches_the_oracle():
     assert np.abs(tw - O.gate_weights(logits, r)).max() <= 1e-6
 
 
+def _lane_order_logits(x, w):
+    """Float64 sums in the kernels' one order: lane l of 64 adds the products of
+    the 8-element chunks l, l + 64, ... (exact in float64) one after the other,
+    then neighbouring lanes are added pairwise up to sixteen, and the four
+    sixteens in order."""
+    x, w = x.astype(np.float64), w.astype(np.float64)
+    T, d = x.shape
+    lanes = np.zeros((T, len(w), 64))
+    for c in range(0, d, 512):
+        n = min(512, d - c) // 8
+        for i in range(8):
+            lanes[:, :, :n] += x[:, None, c + i:c + 8 * n:8] * w[None, :, c + i:c + 8 * n:8]
+    for _ in range(4):
+        lanes = lanes[..., 0::2] + lanes[..., 1::2]
+    s = ((lanes[..., 0] + lanes[..., 1]) + lanes[..., 2]) + lanes[..., 3]
+    return s.astype(np.float32)
+
+
+# Few tokens (a block per token), and a batch that takes the dense kernel with
+# its top-k (16 experts), the dense kernel (the logits wanted, or in the
+# forward's workspace), or the screen.
+@pytest.mark.parametrize("T,E,d", [(600, 16, 1088), (1030, 8, 256), (300, 40, 1088), (300, 200, 7168),
+                                   (270, 300, 192)])
+def test_a_token_gates_alike_in_every_batch(T, E, d):
+    """Terms of 2^40 that cancel leave a logit that depends on the order of the
+    float64 additions: it has to be one order in every kernel."""
+    print(f"[gpu] gate order T={T} E={E} d={d}", flush=True)
+    k = 6
+    x, w = _normal(T, d, E, T + d)
+    w *= 50.0
+    for a, b in ((5, d - 3), (70, 131), (33, 34)):
+        x[:, a] = x[:, b] = 2.0 ** 20
+        w[:, a], w[:, b] = 2.0 ** 20, -(2.0 ** 20)
+    few = 4
+    expected = _lane_order_logits(x[:few].float().cpu().numpy(), w.float().cpu().numpy())
+    exact = x[:few].double().cpu().numpy() @ w.double().cpu().numpy().T
+    assert (exact.astype(np.float32) != expected).any()  # the order shows
+    logits, ids, tw = _run(x[:few].contiguous(), w, k, True)
+    assert np.array_equal(logits.view(np.uint32), expected.view(np.uint32))
+    for want in (True, False):
+        l2, ids2, tw2 = _run(x, w, k, want)
+        if want:
+            assert np.array_equal(l2[:few].view(np.uint32), expected.view(np.uint32))
+        assert np.array_equal(ids2[:few], ids)
+        assert np.array_equal(tw2[:few].view(np.uint32), tw.view(np.uint32))
+    wl = synth.make_custom(T=T, d=d, E=E, k=k, I=1024, n_local=2, shadow_experts=[0], gate="weights",
+                           seed=T, device=DEV)
+    wl.x.copy_(x)
+    wl.wg.copy_(w)
+    f = tg.EwForward(wl)
+    f()
+    torch.cuda.synchronize()
+    assert np.array_equal(host(f.topk_ids)[:few], ids)
+    assert np.array_equal(host(f.topk_w)[:few].view(np.uint32), tw.view(np.uint32))
+
+
 # token (4 tokens), dense with its top-k (16 experts) and after it (logits
 # wanted), screen.
 @pytest.mark.parametrize("T,E", [(4, 40), (600, 16), (300, 200), (300, 300)])
