@@ -13,8 +13,8 @@
 // makes its writes visible system-wide, and then, in a second kernel that
 // starts only after every copy has finished, publishes the commit record:
 // the sequence number after the batch's last, so every number below it has
-// landed. Restoration copies back only the segments numbered below the
-// commit record.
+// landed. Restoration reads the commit record and copies back only the
+// segments numbered below it.
 #include "tg.h"
 #include "tg_device.h"
 #include "tg_launch.h"
@@ -82,33 +82,67 @@ __global__ __launch_bounds__(kBlock) void ckpt_log_commit_kernel(
                        __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Restore: status of segment i, with the commit record as it was read.
+__device__ __forceinline__ uint8_t restore_status(uint64_t committed, uint64_t seq, uint64_t src,
+                                                  uint64_t dst, uint32_t b, uint64_t store_bytes,
+                                                  uint64_t kv_bytes) {
+  if (!seg_ok(src, b, store_bytes) || !seg_ok(dst, b, kv_bytes)) return 2;
+  return seq < committed ? 1 : 0;  // not committed: its bytes may be incomplete
+}
+
+__device__ __forceinline__ uint64_t read_commit(const uint64_t* commit) {
+  return __hip_atomic_load(commit, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// STATUS: the kernel reads the commit record and writes the status itself;
+// otherwise kv_restore_status_kernel ran before it.
+template <bool STATUS>
 __global__ __launch_bounds__(kBlock) void kv_restore_kernel(
     const uint4* store, uint64_t store_bytes, const uint64_t* commit,
     const uint64_t* __restrict__ seq, const uint64_t* __restrict__ src,
     const uint64_t* __restrict__ dst, const uint32_t* __restrict__ bytes, int n,
-    uint4* __restrict__ kv, uint64_t kv_bytes, uint8_t* __restrict__ status) {
-  const uint64_t committed = __hip_atomic_load(commit, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM);
+    uint4* __restrict__ kv, uint64_t kv_bytes, uint8_t* status) {
+  uint64_t committed = 0;
+  if (STATUS) committed = read_commit(commit);
+  else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");  // the store's bytes, from where they are
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const uint32_t b = bytes[i];
-    uint8_t st;
-    if (!seg_ok(src[i], b, store_bytes) || !seg_ok(dst[i], b, kv_bytes)) {
-      st = 2;
-    } else if (seq[i] >= committed) {
-      st = 0;  // not committed: its bytes may be incomplete
-    } else {
-      st = 1;
-      const uint64_t s0 = src[i] / 16, d0 = dst[i] / 16;
-      for (uint32_t c = threadIdx.x; c < b / 16; c += kBlock) kv[d0 + c] = store[s0 + c];
-    }
-    if (threadIdx.x == 0) status[i] = st;
+    const uint64_t s0 = src[i], d0 = dst[i];
+    const uint8_t st =
+        STATUS ? restore_status(committed, seq[i], s0, d0, b, store_bytes, kv_bytes) : status[i];
+    if (st == 1)
+      for (uint32_t c = threadIdx.x; c < b / 16; c += kBlock) kv[d0 / 16 + c] = store[s0 / 16 + c];
+    if (STATUS && threadIdx.x == 0) status[i] = st;
   }
 }
 
-// Blocks of a restore: reads of the host's memory go at the link's rate with
-// this many blocks of 4 waves, and at a fraction of it with more of them
-// competing (4096 segments of 4 KB: 445 us with 16 blocks, 297 with 48, 302
-// with 64, 364 with 256, 679 with 1024, 1660 to 1840 with 4096).
-constexpr int kRestoreBlocks = 48;
+__global__ __launch_bounds__(kBlock) void kv_restore_status_kernel(
+    uint64_t store_bytes, const uint64_t* commit, const uint64_t* __restrict__ seq,
+    const uint64_t* __restrict__ src, const uint64_t* __restrict__ dst,
+    const uint32_t* __restrict__ bytes, int n, uint64_t kv_bytes, uint8_t* __restrict__ status) {
+  __shared__ uint64_t committed;
+  if (threadIdx.x == 0) committed = read_commit(commit);
+  __syncthreads();
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock)
+    status[i] =
+        restore_status(committed, seq[i], src[i], dst[i], bytes[i], store_bytes, kv_bytes);
+}
+
+// A restore of more than kRestoreAlone segments reads the commit record in a
+// kernel of its own, and kRestoreBlocks blocks copy. The record lies across the
+// host's link, where each block's read of it costs about 0.37 us, one after
+// the other, so a copy whose blocks all read it pays for every block. us, all
+// reading it with 4096 blocks, with 48, and this way with 256:
+//   host memory    200 x    4 KB      107    36    29
+//                 4096 x    4 KB     1965   314   310   (the link's rate)
+//   device memory  200 x    4 KB       76    22    12
+//                 4096 x    4 KB     1212    59    24
+//                 1000 x 1024 KB      796  2532   702
+// 512 blocks copy the last in 445, but the 4096 segments from the host in 326.
+// Up to a dozen segments the second launch is the dearer: 8 take 7 us in one
+// kernel and 9 in two, 16 10 and 9.
+constexpr int kRestoreBlocks = 256;
+constexpr int kRestoreAlone = 12;
 
 int grid_for(int n, int max_blocks) { return n < max_blocks ? n : max_blocks; }
 
@@ -148,10 +182,21 @@ hipError_t launch_kv_restore(const void* store, size_t store_bytes, const uint64
                              const uint64_t* seq, const uint64_t* src, const uint64_t* dst,
                              const uint32_t* bytes, int n, void* kv, size_t kv_bytes,
                              uint8_t* status, hipStream_t stream) {
-  if (n > 0)
-    hipLaunchKernelGGL(kv_restore_kernel, dim3(grid_for(n, kRestoreBlocks)), dim3(kBlock), 0, stream,
-                       static_cast<const uint4*>(store), (uint64_t)store_bytes, commit, seq, src,
-                       dst, bytes, n, static_cast<uint4*>(kv), (uint64_t)kv_bytes, status);
+  if (n <= 0) return hipGetLastError();
+  const dim3 grid(grid_for(n, kRestoreBlocks)), block(kBlock);
+  const uint4* const from = static_cast<const uint4*>(store);
+  uint4* const to = static_cast<uint4*>(kv);
+  if (n <= kRestoreAlone) {
+    hipLaunchKernelGGL(kv_restore_kernel<true>, grid, block, 0, stream, from, (uint64_t)store_bytes,
+                       commit, seq, src, dst, bytes, n, to, (uint64_t)kv_bytes, status);
+  } else {
+    hipLaunchKernelGGL(kv_restore_status_kernel, dim3(grid_for((n + kBlock - 1) / kBlock, 16)),
+                       block, 0, stream, (uint64_t)store_bytes, commit, seq, src, dst, bytes, n,
+                       (uint64_t)kv_bytes, status);
+    hipLaunchKernelGGL(kv_restore_kernel<false>, grid, block, 0, stream, from,
+                       (uint64_t)store_bytes, commit, seq, src, dst, bytes, n, to,
+                       (uint64_t)kv_bytes, status);
+  }
   return hipGetLastError();
 }
 

@@ -118,8 +118,9 @@ hipError_t launch_batch_trigger(const uint32_t* delivered, const uint8_t* aw_ali
                                 long long spin_limit, uint8_t* token_valid, int32_t* status,
                                 hipStream_t stream);
 
-// KV-segment checkpoint / restoration (one block per segment; the commit
-// record is written by a second kernel after the copies).
+// KV-segment checkpoint / restoration (a block takes a segment at a time; the
+// commit record is written by a second kernel after the copies, and read by
+// a first one before those of a restore).
 hipError_t launch_kv_checkpoint(const void* kv, size_t kv_bytes, const uint64_t* seg_off,
                                 const uint32_t* seg_bytes, int n, uint64_t first_seq, void* store,
                                 tg_ckpt_record* log, int log_cap, uint64_t* commit, int max_blocks,
