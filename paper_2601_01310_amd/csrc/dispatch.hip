@@ -11,18 +11,15 @@
 //      otherwise given its first live candidate now, to be recomputed;
 //   2. scan: per-slot totals, exclusive slot offsets, and the position of
 //      every (chunk, slot) within its slot in chunk order (the histograms
-//      are slot-major, so one wave scans one slot's chunks). When S times
-//      the number of chunks is at most 16384, each scatter block does this
-//      for itself from the whole histogram instead, and the launch is saved
-//      (40 slots x 256 chunks: 13.9 us in two kernels, 8.5 in one; x 63
-//      chunks 9.6 and 6.2);
+//      are slot-major, so one wave sums one slot's chunks). Each scatter block
+//      does this for itself from the whole histogram;
 //   3. scatter: each wave walks an equal share of a chunk in pair order and
 //      ranks the pairs of each group of 64 by slot: one ballot per bit of
 //      the slot index gives every lane the lanes that share its slot, so the
 //      rank costs the same for any mix of slots, and rows follow
 //      (slot, token, rank).
 // Up to 4096 pairs, one block runs all three passes (the batch of a decode
-// step fits, and two launches are saved; past that the three grids are
+// step fits, and a launch is saved; past that the two grids are
 // faster, as each group of 1024 pairs costs the one block about 1.7 us).
 // The gather then copies one activation row per routed pair with 16-byte
 // loads and stores (rows are contiguous in source and destination, so the
@@ -36,7 +33,8 @@ namespace {
 
 constexpr int kMaxS = 1024;
 constexpr int kBlock = 256;
-constexpr int kFusedScanHist = 16384;  // S * nchunks up to which scatter scans by itself
+constexpr int kSmallHist = 1024;  // entries that a scatter block loads as they lie,
+constexpr int kSmallChunks = 32;  // of at most so many chunks
 
 // Slot of a pair of expert e: the first live ERT candidate of e.
 // REPLAY: -1 also when the first pass's slot pr is still alive (its result
@@ -153,90 +151,20 @@ __global__ __launch_bounds__(kBlock) void remap_count_kernel(
   if (sched && blockIdx.x == 0) zero_claims(sched, threadIdx.x);
 }
 
-// One block of 1024 threads (16 waves). hist[s * nchunks + c] holds the
-// pairs of chunk c on slot s (nchunks <= 4 * 64). Wave w takes slots w,
-// w + 16, ...: lane l sums chunks 4l .. 4l+3, a wave scan gives every chunk
-// its exclusive position within the slot (written back in place, the
-// scatter adds the slot offset), and the slot totals go through a block
-// scan (wave scans and the waves' totals) to the exclusive slot offsets.
-__global__ __launch_bounds__(1024) void scan_kernel(int32_t* __restrict__ hist,
-                                                    const int32_t* __restrict__ unserved_chunk,
-                                                    int nchunks, int S, int32_t* __restrict__ counts,
-                                                    int32_t* __restrict__ offsets,
-                                                    int32_t* __restrict__ n_unserved,
-                                                    int32_t* __restrict__ total_out) {
-  __shared__ int tot[1024];
-  __shared__ int wsum[1024 / kWave];
-  __shared__ int nu;
-  const int tid = threadIdx.x;
-  const int wave = tid / kWave, lane = lane_id();
-  if (tid == 0) nu = 0;
-  for (int s = wave; s < S; s += 1024 / kWave) {
-    int32_t* hs = hist + (size_t)s * nchunks;
-    int v[4], sum = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = 4 * lane + i;
-      v[i] = (c < nchunks) ? hs[c] : 0;
-      sum += v[i];
-    }
-    int incl = sum;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int t = __shfl_up(incl, off);
-      if (lane >= off) incl += t;
-    }
-    int run = incl - sum;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = 4 * lane + i;
-      if (c < nchunks) hs[c] = run;
-      run += v[i];
-    }
-    if (lane == kWave - 1) tot[s] = incl;
-  }
-  int part = 0;
-  for (int c = tid; c < nchunks; c += 1024) part += unserved_chunk[c];
-  __syncthreads();
-  if (part) atomicAdd(&nu, part);
-  // Inclusive scan over the slot totals: a wave scan per 64 slots, then the
-  // totals of the waves before.
-  const int total = (tid < S) ? tot[tid] : 0;
-  int incl = total;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int t = __shfl_up(incl, off);
-    if (lane >= off) incl += t;
-  }
-  if (lane == kWave - 1) wsum[wave] = incl;
-  __syncthreads();
-  for (int w = 0; w < wave; ++w) incl += wsum[w];
-  if (tid < S) {
-    counts[tid] = total;
-    offsets[tid] = incl - total;
-  }
-  if (tid == S - 1) {
-    offsets[S] = incl;
-    if (total_out) total_out[0] = incl;
-  }
-  if (tid == 0) n_unserved[0] = nu;
-}
-
 __device__ __forceinline__ int wave_sum_int(int v) {
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
   return v;
 }
 
-// SCAN false: hist[s * nchunks + c] is the position of chunk c's first pair
-// within slot s and offsets the slot offsets (both from scan_kernel).
-// SCAN true: hist holds the per-chunk counts of remap_count, and every block
-// derives what it needs itself (its chunk's position in each slot and the
-// slot offsets, from all of hist; for small S * nchunks this is cheaper
-// than a launch); block 0 also writes counts, offsets, the unserved count
-// and the total. sbits: bits of the largest slot index. With a schedule area
-// one block more than there are chunks is launched, which plans the GEMMs.
-template <bool SCAN>
+// hist holds the per-chunk counts of remap_count (slot-major), and every block
+// derives its chunk's position in each slot and the slot offsets itself, from
+// all of it; block 0 also writes counts, offsets, the unserved count and the
+// total. sbits: bits of the largest slot index. With a schedule area one block
+// more than there are chunks is launched, which plans the GEMMs. CH: chunks
+// per lane, nchunks <= 64 CH; 0 for at most kSmallHist entries, and at most
+// kSmallChunks per slot.
+template <int CH>
 __global__ __launch_bounds__(kBlock) void scatter_kernel(
     const int32_t* __restrict__ pair_slot, int npairs, int S, int nchunks, int sbits,
     const int32_t* __restrict__ hist, const int32_t* __restrict__ unserved_chunk,
@@ -246,63 +174,92 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(
     int32_t* __restrict__ sched, GemmDims dims) {
   constexpr int kWaves = kBlock / kWave;
   __shared__ int cnt[kWaves][kMaxS];
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = lane_id();
   const bool planner = (int)blockIdx.x == nchunks;
-  if (!SCAN && planner) {
-    plan_gemms<true>(wave, S, [&](int s) { return offsets[s + 1] - offsets[s]; }, sched, dims);
-    return;
-  }
   // The chunk's pairs are split evenly (in multiples of 64) over the waves.
   const int c0 = blockIdx.x * chunk;
   const int n_c = min(chunk, npairs - c0);
   const int span = ((n_c + kWaves * kWave - 1) / (kWaves * kWave)) * kWave;
   const int p0 = c0 + wave * span;
   const int p1 = min(c0 + n_c, p0 + span);
-  __shared__ int base[SCAN ? kMaxS : 1];  // first row of this chunk's pairs on each slot
-  __shared__ int tot[SCAN ? kMaxS : 1];
+  __shared__ int base[kMaxS];  // first row of this chunk's pairs on each slot
+  __shared__ int tot[kMaxS];
   __shared__ int wsum[kWaves];
   for (int s = lane; s < S; s += kWave) cnt[wave][s] = 0;
-  if (SCAN) {
-    // Wave w takes slots w, w + 4, ..., kGroup of them at a time so that their
-    // loads are in flight together: lane l holds chunks l, l + 64, ... of each;
-    // the sums over all chunks and over the chunks before this one are DPP
-    // reductions.
-    constexpr int kGroup = 4, kPer = kDispatchChunks / kWave;
-    for (int s0 = wave; s0 < S; s0 += kGroup * kWaves) {
-      int v[kGroup][kPer];
+  // A small histogram is loaded as it lies, four entries per thread at once, and
+  // summed by LDS atomics (integers: their order does not matter). Otherwise
+  // wave w takes slots w, w + 4, ..., kGroup of them at a time so that their
+  // loads are in flight together, 16 whatever CH is: lane l holds chunks l,
+  // l + 64, ... of each; the sums over all chunks and over the chunks before
+  // this one are DPP reductions. The chain of loads bounds it. Against a kernel
+  // of one block between count and scatter (17 to 64 chunks; 128; 256), us for
+  // the whole dispatch without the row copy: 40 slots 10 -> 8, 10 -> 9,
+  // 12 -> 10; 200 slots 17 -> 15, 19 -> 17, 29 -> 20; 1024 slots 48 -> 43,
+  // 62 -> 57, 110 -> 77. (With the loads of 256 chunks for any number of them,
+  // four slots at a time, 200 slots of 17 to 64 chunks took 18 and 960 of 17
+  // took 57.) For 24 to 60 slots of 17 chunks the atomics are 0.5 to 1.2 us
+  // faster than the reductions, for 1 to 16 of up to 32 chunks 0.3; 16 slots of
+  // 64 chunks, whose entries of a wave meet in one slot, are 0.8 slower.
+  if (CH == 0) {
+    constexpr int kPer = kSmallHist / kBlock;
+    const int nh = S * nchunks;
+    int v[kPer];
 #pragma unroll
-      for (int g = 0; g < kGroup; ++g)
+    for (int q = 0; q < kPer; ++q) {
+      const int j = threadIdx.x + q * kBlock;
+      v[q] = j < nh ? hist[j] : 0;
+    }
+    for (int s = threadIdx.x; s < S; s += kBlock) {
+      tot[s] = 0;
+      base[s] = 0;
+    }
+    __syncthreads();
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-          const int s = s0 + g * kWaves, c = lane + q * kWave;
-          v[g][q] = s < S && c < nchunks ? hist[(size_t)s * nchunks + c] : 0;
-        }
+    for (int q = 0; q < kPer; ++q) {
+      const int j = threadIdx.x + q * kBlock;
+      if (v[q]) {
+        const int s = j / nchunks, c = j - s * nchunks;
+        atomicAdd(&tot[s], v[q]);
+        if (c < (int)blockIdx.x) atomicAdd(&base[s], v[q]);
+      }
+    }
+  }
+  constexpr int kLanes = CH ? CH : 1, kGroup = 16 / kLanes;
+  for (int s0 = wave; CH && s0 < S; s0 += kGroup * kWaves) {
+    int v[kGroup][kLanes];
 #pragma unroll
-      for (int g = 0; g < kGroup; ++g) {
-        const int s = s0 + g * kWaves;
-        int all = 0, before = 0;
+    for (int g = 0; g < kGroup; ++g)
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-          all += v[g][q];
-          before += lane + q * kWave < (int)blockIdx.x ? v[g][q] : 0;
-        }
-        all = wave_reduce<false>(all);
-        before = wave_reduce<false>(before);
-        if (lane == 0 && s < S) {
-          tot[s] = all;
-          base[s] = before;
-        }
+      for (int q = 0; q < kLanes; ++q) {
+        const int s = s0 + g * kWaves, c = lane + q * kWave;
+        v[g][q] = s < S && c < nchunks ? hist[(size_t)s * nchunks + c] : 0;
+      }
+#pragma unroll
+    for (int g = 0; g < kGroup; ++g) {
+      const int s = s0 + g * kWaves;
+      if (s >= S) break;
+      int all = 0, before = 0;
+#pragma unroll
+      for (int q = 0; q < kLanes; ++q) {
+        all += v[g][q];
+        before += lane + q * kWave < (int)blockIdx.x ? v[g][q] : 0;
+      }
+      all = wave_reduce<false>(all);
+      before = wave_reduce<false>(before);
+      if (lane == 0) {
+        tot[s] = all;
+        base[s] = before;
       }
     }
   }
   __syncthreads();
-  if (SCAN && planner) {
+  if (planner) {
     plan_gemms<true>(wave, S, [&](int s) { return tot[s]; }, sched, dims);
     return;
   }
-  if (SCAN) {
-    // Exclusive scan of the slot totals: thread i holds slots 4i .. 4i+3.
+  // Exclusive scan of the slot totals: thread i holds slots 4i .. 4i+3.
+  {
     int v[4], sum = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -351,7 +308,7 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(
   }
   __syncthreads();
   for (int s = threadIdx.x; s < S; s += kBlock) {
-    int run = SCAN ? base[s] : offsets[s] + hist[(size_t)s * nchunks + blockIdx.x];
+    int run = base[s];
     for (int w = 0; w < kWaves; ++w) {
       const int v = cnt[w][s];
       cnt[w][s] = run;
@@ -616,51 +573,35 @@ hipError_t remap_dispatch(bool replay, const int32_t* ids, int T, int k, const i
                          ids, npairs, k, ert, E, R, alive, S, sbits, token_valid, nullptr,
                          pair_slot, counts, offsets, perm, pair_row, n_unserved, total_out, sched,
                          dims);
-    if (x_perm && npairs > 0) {
-      const int nch = d / 8;
-      const long maxq = (long)npairs * nch;
-      const long blocks = (maxq + kBlock - 1) / kBlock;
-      const int grid = (int)(blocks < 8192 ? blocks : 8192);
-      hipLaunchKernelGGL(gather_kernel, dim3(grid), dim3(kBlock), 0, stream,
-                         reinterpret_cast<const uint4*>(x), perm, offsets, S, k, nch,
-                         reinterpret_cast<uint4*>(x_perm));
-    }
-    return hipGetLastError();
-  }
-  if (nchunks > 0) {
+  } else {
     if (replay)
-      hipLaunchKernelGGL(remap_count_kernel<true>, dim3(nchunks), dim3(kBlock), 0, stream, ids,
-                         npairs, k, ert, E, R, alive, S, nullptr, prior, pair_slot, hist,
-                         unserved_chunk, chunk, sched);
+      hipLaunchKernelGGL(remap_count_kernel<true>, dim3(nchunks), dim3(kBlock), 0, stream, ids, npairs,
+                         k, ert, E, R, alive, S, nullptr, prior, pair_slot, hist, unserved_chunk,
+                         chunk, sched);
     else
       hipLaunchKernelGGL(remap_count_kernel<false>, dim3(nchunks), dim3(kBlock), 0, stream, ids,
                          npairs, k, ert, E, R, alive, S, token_valid, nullptr, pair_slot, hist,
                          unserved_chunk, chunk, sched);
-  }
-  // A small histogram is scanned by every scatter block (one launch less).
-  const bool fused_scan = nchunks > 0 && (long)S * nchunks <= (long)kFusedScanHist;
-  if (!fused_scan)
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, stream, hist, unserved_chunk, nchunks,
-                       S, counts, offsets, n_unserved, total_out);
-  if (nchunks > 0) {
     const dim3 grid(nchunks + (sched ? 1 : 0));
-    if (fused_scan)
-      hipLaunchKernelGGL(scatter_kernel<true>, grid, dim3(kBlock), 0, stream, pair_slot, npairs, S,
-                         nchunks, sbits, hist, unserved_chunk, counts, offsets, n_unserved,
-                         total_out, perm, pair_row, chunk, sched, dims);
-    else
-      hipLaunchKernelGGL(scatter_kernel<false>, grid, dim3(kBlock), 0, stream, pair_slot, npairs, S,
-                         nchunks, sbits, hist, unserved_chunk, counts, offsets, n_unserved,
-                         total_out, perm, pair_row, chunk, sched, dims);
-    if (x_perm) {
-      const int nch = d / 8;
-      const long maxq = (long)npairs * nch;
-      const long blocks = (maxq + kBlock - 1) / kBlock;
-      const int grid = (int)(blocks < 8192 ? blocks : 8192);
-      hipLaunchKernelGGL(gather_kernel, dim3(grid), dim3(kBlock), 0, stream,
-                         reinterpret_cast<const uint4*>(x), perm, offsets, S, k, nch,
-                         reinterpret_cast<uint4*>(x_perm));
-    }
+    // The fewest chunks per lane, so that more slots' loads are in flight.
+#define TG_SCATTER(CH)                                                                          \
+  hipLaunchKernelGGL(scatter_kernel<CH>, grid, dim3(kBlock), 0, stream, pair_slot, npairs, S,   \
+                     nchunks, sbits, hist, unserved_chunk, counts, offsets, n_unserved, total_out, \
+                     perm, pair_row, chunk, sched, dims)
+    if (nchunks <= kSmallChunks && S * nchunks <= kSmallHist) TG_SCATTER(0);
+    else if (nchunks <= kWave) TG_SCATTER(1);
+    else if (nchunks <= 2 * kWave) TG_SCATTER(2);
+    else TG_SCATTER(kDispatchChunks / kWave);
+#undef TG_SCATTER
+  }
+  if (x_perm && npairs > 0) {
+    const int nch = d / 8;
+    const long maxq = (long)npairs * nch;
+    const long blocks = (maxq + kBlock - 1) / kBlock;
+    const int grid = (int)(blocks < 8192 ? blocks : 8192);
+    hipLaunchKernelGGL(gather_kernel, dim3(grid), dim3(kBlock), 0, stream,
+                       reinterpret_cast<const uint4*>(x), perm, offsets, S, k, nch,
+                       reinterpret_cast<uint4*>(x_perm));
   }
   return hipGetLastError();
 }

@@ -1,6 +1,8 @@
-"""Dispatch around the size up to which the scatter blocks scan the histogram
-themselves (slots x chunks <= 16384, chunks of 256 pairs, at most 256 of them):
-routing, counts, offsets and rows bit for bit against the oracle."""
+"""Dispatch in chunks (beyond 4096 pairs; chunks of 256 pairs, at most 256 of
+them), where every scatter block scans the histogram: as it lies (up to 1024
+entries and 32 chunks), or one, two or four chunks per lane, slots in groups of
+64, 32 or 16. Routing, counts, offsets and rows bit
+for bit against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -15,7 +17,12 @@ DEV = "cuda"
 
 @pytest.mark.parametrize("T,k,S", [(8192, 8, 64), (8192, 8, 65), (8190, 8, 3), (2731, 6, 250),
                                    (2731, 6, 256), (4097, 1, 1), (4097, 1, 1000), (700, 7, 40),
-                                   (16384, 8, 40)])
+                                   (16384, 8, 40),
+                                   # 64 | 65, 128 | 129 chunks
+                                   (2048, 8, 63), (2048, 8, 1000), (16385, 1, 129), (4096, 8, 33),
+                                   (4096, 8, 1024), (32769, 1, 17), (5462, 6, 1000), (13107, 5, 256),
+                                   # 32 | 33 chunks, 1024 | more entries
+                                   (1024, 8, 32), (1024, 8, 33), (8193, 1, 31), (4352, 1, 60), (4352, 1, 61)])
 def test_dispatch_matches_the_oracle(T, k, S):
     print(f"[gpu] dispatch scan T={T} k={k} S={S}", flush=True)
     rng = np.random.default_rng(T + S)

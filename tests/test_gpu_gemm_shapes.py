@@ -83,11 +83,12 @@ def test_every_shape_gives_the_bits_of_the_full_tiles(i):
             at += c
 
 
-# One block dispatches up to 4096 pairs; beyond, the scatter plans the GEMMs
-# in a block of its own, with the scan in the scatter (S x chunks <= 1024) or
-# before it.
+# One block dispatches up to 4096 pairs, and a second one chooses the shapes;
+# beyond, the scatter plans the GEMMs in a block of its own, from the histogram
+# in one, two or four chunks per lane.
 @pytest.mark.parametrize("d,I,counts", [c for c in CASES[::4]] + [
-    (128, 192, [241] * 18), (128, 128, [0] * 20 + [97, 96, 31, 1] * 22), (192, 128, [33] * 130)])
+    (128, 192, [241] * 18), (128, 128, [0] * 20 + [97, 96, 31, 1] * 22), (192, 128, [33] * 130),
+    (128, 128, [5] * 900), (128, 128, [400] * 60), (192, 128, [1, 0, 70, 500] * 70)])
 def test_the_forward_plans_its_gemms_as_the_full_tiles(d, I, counts):
     print(f"[gpu] gemm shapes in the forward d={d} I={I} S={len(counts)} P={sum(counts)}", flush=True)
     E, T = len(counts), sum(counts)
