@@ -15,9 +15,9 @@
 //
 // Top-k (larger float32 logit first, ties to the lower expert id) counts, for
 // each of a few candidates, the ones that beat it, or, over more of them or
-// all, takes k rounds of a wave arg-max (the cross-lane step in DPP row
-// operations and lane reads). Lane j holds the j-th winner, the k exponentials
-// are formed in parallel and summed in rank order.
+// all, takes k rounds of an arg-max over a wave or a 16-lane row of it (the
+// cross-lane step in DPP row operations and lane reads). Lane j holds the j-th
+// winner; the k exponentials are summed in rank order.
 #include <type_traits>
 
 #include "tg_device.h"
@@ -644,27 +644,20 @@ __global__ __launch_bounds__(256) void logits_topk_kernel(const float* __restric
 }
 
 // Logits mode for E <= 256 and k <= 16: four tokens per wave, one 16-lane
-// DPP row per token. Lane l of a row holds the candidates l, l + 16, ... of
-// its token in registers, in two halves with a maximum each. tau, the k-th
-// largest of the row's (up to) 32 half maxima, or lower where some are equal,
-// is reached by at least k candidates, so only candidates >= tau can be
-// chosen: k and a few more. They are gathered into the row's lanes through
-// LDS as 64-bit keys: the float32 logit in an order-preserving encoding (-0
-// taken as +0) above the complement of the expert id, so a larger key is a
-// larger logit or, on equal logits, a lower id, and no two keys are equal. A
-// lane's rank is the number of larger keys among the row's 16, and the lanes
-// take their candidates in rank order. With more than 16 candidates (many
-// equal logits, or NaN among them) the wave finds the winners round by round
-// instead: every lane's largest key below the previous winner's, reduced over
-// the row. Either way every lane sums the k exponentials in rank order, the
-// same sum as the one-token-per-wave kernel. Against the rounds alone (the
-// vector ALU's 1270 instructions per wave), 256 experts, top-8: 16384 tokens
-// 19.8 -> 11.5 us; 2011 tokens 8.9 -> 5.6 us and 128 tokens 8.4 -> 5.1 us (one
-// token per wave before).
+// DPP row per token; lane l of a row holds the candidates l, l + 16, ... of its
+// token in registers. A candidate's 64-bit key is the float32 logit in an
+// order-preserving encoding (-0 taken as +0) above the complement of the
+// expert id, so a larger key is a larger logit or, on equal logits, a lower
+// id, and no two keys are equal. Two kernels, chosen by launch_logits_topk:
+//   rounds  takes every lane's largest key below the previous winner's, k
+//           times, reduced over the row with the four DPP row steps;
+//   rows    counts larger keys among a few candidates instead.
+// Both sum the k exponentials in rank order, the same sum as the
+// one-token-per-wave kernel.
 //
 // skip_nan: a NaN logit is never chosen, as in wave_topk, and a choice left
 // empty for it has id 0x7fffffff. Otherwise NaN logits are ordered by their
-// bits (the positive ones above +inf).
+// bits (the positive ones above +inf, the negative ones below -inf).
 constexpr int kRowTokens = 4;  // tokens per wave
 
 __device__ __forceinline__ uint64_t topk_key(float v, int e) {
@@ -706,6 +699,63 @@ __device__ __forceinline__ float row_max_f32(float v) {
   return fmaxf(v, __int_as_float(TG_ROW_MOV(__float_as_int(v), 0x140)));
 }
 
+// k rounds; the vector ALU bounds it, NQ + 4 64-bit maxima a round. (SKIP at run
+// time cost 100000 tokens of 8 experts, k = 1, 6.7 us instead of 5.5.)
+template <int NQ, bool SKIP>
+__global__ __launch_bounds__(256) void logits_topk_rounds_kernel(const float* __restrict__ logits,
+                                                                 int T, int E, int k,
+                                                                 int32_t* __restrict__ ids,
+                                                                 float* __restrict__ w) {
+  const int lane = lane_id();
+  const int l16 = lane & 15;
+  const int t = (blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave) * kRowTokens + (lane >> 4);
+  const bool on = t < T;
+  uint64_t key[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int e = l16 + 16 * q;
+    key[q] = 0;  // no candidate
+    if (on && e < E) {
+      const float v = logits[(size_t)t * E + e];
+      key[q] = SKIP && v != v ? 0 : topk_key(v, e);
+    }
+  }
+  // An empty choice: value -inf, id 0x7fffffff, a key below those of -inf logits.
+  constexpr uint64_t empty = SKIP ? 0x007fffff80000000ull : 0;
+  uint64_t thr = ~0ull;
+  float my_v = 0.0f, v0 = 0.0f, z = 0.0f;
+  int my_id = 0;
+  for (int j = 0; j < k; ++j) {
+    uint64_t best = empty;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) best = (key[q] < thr && key[q] > best) ? key[q] : best;
+    best = row_max_key(best);  // every lane of the row: this round's winner
+    thr = best;
+    const float bv = key_value(best);
+    if (j == 0) v0 = bv;
+    const float ex = expf(bv - v0);
+    z += ex;
+    if (l16 == j) {
+      my_v = ex;
+      my_id = (int)(0xffffffffu - (uint32_t)best);
+    }
+  }
+  if (on && l16 < k) {
+    ids[(size_t)t * k + l16] = my_id;
+    w[(size_t)t * k + l16] = my_v / z;
+  }
+}
+
+// tau, the k-th largest of the row's (up to) 32 half maxima (each lane's
+// candidates alternate between two halves, which are even for any E: with the
+// lower and the upper half of NQ, 16384 tokens of 160 experts, k = 8, took 8.4 us
+// instead of 6.2), or lower where some are equal, is reached by at least k
+// candidates, so only candidates >= tau can be chosen: k and a few more. They are gathered into the row's lanes through LDS, a lane's rank is
+// the number of larger keys among the row's 16, and the lanes take their
+// candidates in rank order. With more than 16 candidates in one of the wave's
+// rows (k near 16, many equal logits, or NaN among them) the wave finds the
+// winners round by round after all, having formed tau for nothing: 10 to 30 %
+// slower than the other kernel.
 template <int NQ>
 __global__ __launch_bounds__(256) void logits_topk_rows_kernel(const float* __restrict__ logits,
                                                                int T, int E, int k,
@@ -727,7 +777,7 @@ __global__ __launch_bounds__(256) void logits_topk_rows_kernel(const float* __re
   float m0 = -__builtin_inff(), m1 = m0;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
-    if (q < (NQ + 1) / 2) m0 = fmaxf(m0, v[q]);
+    if (q % 2 == 0) m0 = fmaxf(m0, v[q]);
     else m1 = fmaxf(m1, v[q]);
   }
   float tau = 0.0f;
@@ -823,20 +873,51 @@ void launch_screen(const uint16_t* x, const uint16_t* wg, int T, int d, int E, i
 
 void launch_logits_topk(const float* logits, int T, int E, int k, int32_t* ids, float* w,
                         bool skip_nan, hipStream_t stream) {
-  if (E <= 256 && k <= 16) {
+  // us at 2048 | 16384 | 100000 tokens: one token per wave, rounds, rows
+  //   256 experts  k = 1    3.2  3.4  4.2 |  -  5.0  5.6 |  -   25   21
+  //                k = 3    4.3  4.2  4.5 |  -  6.5  5.9 |  -   31   22
+  //                k = 8    7.1  6.7  5.1 |  -   11  6.7 |  -   47   26
+  //                k = 11   8.8  7.8  8.9 |  -   13   13 |  -   58   39
+  //                k = 16    12  9.6   11 |  -   17   19 |  -   79   89
+  //   8 experts    k = 2    3.0  2.6  2.9 |  -  3.0  3.8 |  -  7.6   11
+  //                k = 4    3.7  3.0  3.0 |  -  3.8  4.1 |  -   12   13
+  //                k = 8    5.3  3.7  3.3 |  -  5.6  4.7 |  -   22   16
+  // Rounds cost in proportion to k and, beyond a few ten thousand tokens, where
+  // the vector ALU is full, to E. Rows cost little until a wave's candidates
+  // are too many: never with 32 experts, each a half's maximum, else from about
+  // ten choices on, which delays all of a small batch but few waves of a large
+  // one. A wave per token is the shortest chain for a few rounds over many
+  // experts while there are waves to spare.
+  const bool wave = T < 4096 && E > 64 && k <= (E > 128 ? 3 : 2);
+  if (E <= 256 && k <= 16 && !wave) {
     // Few tokens: one wave per block, so that more CUs take part.
     const int waves = T >= 4096 ? 4 : 1;
     const int per_block = waves * kRowTokens;
     const dim3 grid((T + per_block - 1) / per_block), block(64 * waves);
-    if (E <= 64)
-      hipLaunchKernelGGL(logits_topk_rows_kernel<4>, grid, block, 0, stream, logits, T, E, k, ids,
-                         w, skip_nan);
-    else if (E <= 128)
-      hipLaunchKernelGGL(logits_topk_rows_kernel<8>, grid, block, 0, stream, logits, T, E, k, ids,
-                         w, skip_nan);
-    else
-      hipLaunchKernelGGL(logits_topk_rows_kernel<16>, grid, block, 0, stream, logits, T, E, k, ids,
-                         w, skip_nan);
+    const int least = E <= 64 ? 5 : T > 32768 ? 1 : E <= 128 ? 4 : 3;
+    const int most = E <= 32 ? 16 : T > 32768 ? 12 : T > 8192 ? 11 : E <= 64 ? 10 : 9;
+    const bool rows = k >= least && k <= most;
+#define TG_ROWS(NQ)                                                                      \
+  hipLaunchKernelGGL(logits_topk_rows_kernel<NQ>, grid, block, 0, stream, logits, T, E, k, \
+                     ids, w, skip_nan)
+#define TG_ROUNDS(NQ, SKIP)                                                                   \
+  hipLaunchKernelGGL((logits_topk_rounds_kernel<NQ, SKIP>), grid, block, 0, stream, logits, T, \
+                     E, k, ids, w)
+    if (rows) {
+      if (E <= 64) TG_ROWS(4);
+      else if (E <= 128) TG_ROWS(8);
+      else TG_ROWS(16);
+    } else if (skip_nan) {
+      if (E <= 64) TG_ROUNDS(4, true);
+      else if (E <= 128) TG_ROUNDS(8, true);
+      else TG_ROUNDS(16, true);
+    } else {
+      if (E <= 64) TG_ROUNDS(4, false);
+      else if (E <= 128) TG_ROUNDS(8, false);
+      else TG_ROUNDS(16, false);
+    }
+#undef TG_ROWS
+#undef TG_ROUNDS
   } else {
     hipLaunchKernelGGL(logits_topk_kernel, dim3((T + kWaves - 1) / kWaves), dim3(256), 0, stream,
                        logits, T, E, k, ids, w);

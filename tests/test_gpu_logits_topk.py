@@ -39,6 +39,25 @@ def test_random_logits(T, E, k):
     _check(torch.randn((T, E), generator=g, device=DEV), k)
 
 
+# At the limits between the kernels: one token per wave (under 4096 tokens, more
+# than 64 experts, 2 or 3 choices), rounds, and a few candidates (from 3 to 5
+# choices on, up to 9 to 12 of more than 32 experts).
+@pytest.mark.parametrize("T,E,k", [
+    (700, 64, 2), (700, 65, 2), (700, 65, 3), (700, 128, 3), (700, 128, 4), (700, 129, 3), (700, 129, 4), (4095, 200, 1),
+    (4096, 200, 1), (4096, 200, 3), (700, 64, 4), (700, 64, 5), (700, 32, 16), (700, 33, 10),
+    (700, 33, 11), (700, 65, 9), (700, 65, 10), (700, 250, 16), (8192, 100, 10), (8193, 100, 11),
+    (8193, 100, 12), (32768, 129, 2), (32769, 129, 1), (32769, 129, 12), (32769, 40, 13), (32769, 8, 4)])
+def test_limits_between_the_kernels(T, E, k):
+    print(f"[gpu] logits topk limits T={T} E={E} k={k}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T + E + k)
+    lg = torch.randn((T, E), generator=g, device=DEV)
+    lg[0::7] = torch.round(lg[0::7])
+    lg[1::7] = 0.5
+    lg[2::7, k:] = -float("inf")
+    _check(lg, k)
+
+
 @pytest.mark.parametrize("E,k", [(40, 8), (100, 8), (256, 8), (256, 16)])
 def test_ties_and_masks(E, k):
     print(f"[gpu] logits topk ties E={E} k={k}", flush=True)
@@ -60,7 +79,8 @@ def test_ties_and_masks(E, k):
 # NaN logits are never chosen by batches under 4096 tokens or beyond 256
 # experts; where fewer than k are left, the id is 0x7fffffff, the weight 0 (NaN
 # without any).
-@pytest.mark.parametrize("T,E,k", [(5, 40, 8), (70, 256, 8), (4095, 128, 16), (4100, 300, 4)])
+@pytest.mark.parametrize("T,E,k", [(5, 40, 8), (70, 256, 8), (4095, 128, 16), (4100, 300, 4),
+                                   (70, 64, 3), (70, 200, 3), (700, 256, 12)])
 def test_nan_is_not_chosen(T, E, k):
     print(f"[gpu] logits topk NaN T={T} E={E} k={k}", flush=True)
     g = torch.Generator(device=DEV)
@@ -90,6 +110,22 @@ def check_without_nan(l, k, ids, w):
     top = np.where(left, np.take_along_axis(l, r, 1).astype(np.float64), -np.inf)[some]
     e = np.exp(top - top[:, :1])
     assert np.abs(w[some] - e / e.sum(1, keepdims=True)).max() <= 1e-6
+
+
+@pytest.mark.parametrize("k", [3, 5])
+def test_nan_is_ordered_in_large_batches_by_either_kernel(k):
+    """As below, by rounds and among a few candidates, down to the negative NaN."""
+    print(f"[gpu] logits topk NaN order k={k}", flush=True)
+    T = 4100
+    lg = torch.full((T, 40), -float("inf"), device=DEV)
+    lg[:, 11] = float("nan")
+    lg.view(torch.int32)[:, :37] = torch.where(lg[:, :37].isnan(), lg.view(torch.int32)[:, :37], -4194304)
+    lg[:, 38] = 2.0
+    ids = torch.full((T, k), -7, dtype=torch.int32, device=DEV)
+    w = torch.empty((T, k), dtype=torch.float32, device=DEV)
+    tg.tg_gate_topk(None, None, lg, T, 0, 40, k, None, ids, w)
+    torch.cuda.synchronize()
+    assert (host(ids) == np.array([11, 38, 37, 39, 0][:k])).all()
 
 
 def test_nan_is_ordered_in_large_batches():
