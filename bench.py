@@ -27,7 +27,7 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 RIDGE_FLOP_PER_BYTE = PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
 STAGES = ["gate", "dispatch", "ffn_gateup", "ffn_down", "combine"]
 GEMM_SRC = [os.path.join(ROOT, "paper_2601_01310_amd", "csrc", f)
-            for f in ("grouped_gemm.hip", "tg_device.h")]
+            for f in ("grouped_gemm.hip", "tg_device.h", "tg_shapes.h")]
 TRAFFIC = os.path.join(ROOT, "profiles", "gemm_traffic.json")
 
 

@@ -1,5 +1,6 @@
 """Host-side parts of bench.py: the CPU baseline leg and the one-GPU limit."""
 import os
+import re
 import subprocess
 import sys
 
@@ -46,6 +47,22 @@ def test_kernel_source_hash_ignores_comments_but_not_code(tmp_path):
     assert bench.kernel_source_hash([str(a)]) == h0
     a.write_text("int f(int x) {\n  return x + 2;\n}\n")
     assert bench.kernel_source_hash([str(a)]) != h0
+
+
+def test_the_traffic_hash_covers_the_gemms_device_code():
+    """Every file with device code that the GEMM's source includes, so that a
+    change of its tiles leaves no old figure standing."""
+    csrc = os.path.join(ROOT, "paper_2601_01310_amd", "csrc")
+    seen, todo = set(), ["grouped_gemm.hip"]
+    while todo:
+        name = todo.pop()
+        if name in seen or not os.path.exists(os.path.join(csrc, name)):
+            continue
+        seen.add(name)
+        text = open(os.path.join(csrc, name), encoding="utf-8").read()
+        todo += re.findall(r'#include "([^"]+)"', text)
+    device = {f for f in seen if "__device__" in open(os.path.join(csrc, f), encoding="utf-8").read()}
+    assert device == {os.path.basename(f) for f in bench.GEMM_SRC}
 
 
 def test_gateup_roofline_picks_the_bound_by_arithmetic_intensity():
