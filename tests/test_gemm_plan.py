@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from tests import _hip_host
+from tests.test_gpu_gemm_shapes import CASES, FORWARDS
 
 WORDS, PLAN = 16, 9  # words per GEMM in the schedule area, and before its plan
 HEIGHTS = (32, 64, 128, 256)
@@ -54,3 +55,23 @@ def test_a_mask_written_during_the_dispatch_leaves_plan_and_offsets_in_agreement
             assert (words[:PLAN] == 0).all()
             assert 0 <= words[PLAN] <= 8
             assert words[PLAN + 1:PLAN + 5].tolist() == [int((-(-rows // h)).sum()) for h in HEIGHTS]
+
+
+SHAPES = ("32x64", "32x32", "64x128", "64x64", "128x128", "128x64", "128x256", "32", "256")
+
+
+def _shapes(lib, d, I, rows):
+    r = np.array(rows, np.int32)
+    return tuple(SHAPES[lib.choose(up, _p(r), len(r), 256, K, cols)]
+                 for up, K, cols in ((1, d, I), (0, I, d)))
+
+
+def test_the_shape_cases_take_the_shapes_that_they_name(plan):
+    """The GPU tests compare a launch's own choice with the full tiles bit for
+    bit; a case whose choice had become the full tiles would compare them with
+    themselves. The base shapes are reached by many other tests too."""
+    for cases in (CASES, FORWARDS):
+        for d, I, rows, up, down in cases:
+            assert _shapes(plan, d, I, rows) == (up, down), (d, I, rows)
+        for g in (3, 4):
+            assert set(SHAPES) - {c[g] for c in cases} <= {"32", "256"}
