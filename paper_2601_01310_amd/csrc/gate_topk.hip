@@ -271,11 +271,14 @@ __device__ __forceinline__ int run_of_logits(const uint4* __restrict__ xr,
 // 2.5 * 2^-23 * a for an instruction's 32 products.) A bound that is not
 // finite keeps its expert.
 //
-// Selection: tau, the k-th largest s~ - B, is at most the k-th largest exact
-// logit, so an expert with s~ + B < tau cannot be chosen, nor tie. The
-// others (k and, for independent inputs, less than one more) get their
-// float64 logits, one wave per token, and the top-k runs over those: ids and
-// weights have the bits that all E float64 logits would give.
+// Selection: tau, the k-th largest of the 64 lanes' largest s~ - B (lane l
+// holds experts l, l + 64, ...), is reached by k experts and so at most the
+// k-th largest exact logit: an expert with s~ + B < tau cannot be chosen, nor
+// tie. The others get their float64 logits, one wave per token, and the top-k
+// runs over those: ids and weights have the bits that all E float64 logits
+// would give. For independent logits of more than 64 experts these are the
+// sum of 64 / (64 - i) over i < k, as two of the largest may share a lane, and
+// what the bounds leave open: 8.5 for k = 8, 18 for 16, 44 for 32.
 //
 // Both operands go global -> LDS with buffer loads that write LDS directly,
 // 128 bytes of a row at a time, through a ring of NB stage buffers; 16-byte

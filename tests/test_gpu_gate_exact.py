@@ -4,8 +4,8 @@ Token and gate rows are built so that each exact dot product lies 2^-40
 above, exactly on, or 2^-40 below a float32 midpoint, behind a +1024 /
 -1024 pair that a float32 running sum would lose the small terms to; the
 expected logits are the correctly rounded values from exact rational
-arithmetic. The three weight-mode paths of the gate (matrix staged in LDS
-widened to float32, staged as bf16, read from memory) must return them bit
+arithmetic. The weight-mode paths of the gate that return logits (one token
+per block; float64 MFMA, with its top-k or before it) must return them bit
 for bit; so must the full-size Mixtral workload as generated on the GPU,
 whose every logit rounds the same in any float64 summation order.
 """
@@ -35,11 +35,14 @@ def _gate(x_bits, w_bits, k):
     return host(logits), host(ids), host(tw)
 
 
-@pytest.mark.parametrize("T,E,d", [(45, 8, 256), (40, 8, 5120), (37, 16, 4096)],
-                         ids=["staged_f32", "staged_bf16", "unstaged"])
-def test_logits_at_float32_midpoints_are_correctly_rounded(T, E, d):
-    print(f"[gpu] gate midpoints T={T} E={E} d={d}", flush=True)
+# copies: the same tokens many times over, for the kernels of larger batches.
+@pytest.mark.parametrize("T,E,d,copies", [
+    (45, 8, 256, 1), (40, 8, 5120, 1), (37, 16, 4096, 1), (45, 8, 256, 23), (37, 16, 4096, 14),
+    (40, 32, 4096, 7)], ids=["token", "token_long", "token_16", "mfma_topk", "mfma_topk_16", "mfma"])
+def test_logits_at_float32_midpoints_are_correctly_rounded(T, E, d, copies):
+    print(f"[gpu] gate midpoints T={T} E={E} d={d} copies={copies}", flush=True)
     x, w, expected, delta = C.engineered(T, E, d, seed=T * 1000 + d)
+    x, expected, delta = (np.tile(a, (copies, 1)) for a in (x, expected, delta))
     k = 2
     logits, ids, tw = _gate(x, w, k)
     bad = logits.view(np.uint32) != expected.view(np.uint32)
