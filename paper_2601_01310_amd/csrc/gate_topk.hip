@@ -268,7 +268,8 @@ __device__ __forceinline__ int run_of_logits(const uint4* __restrict__ xr,
 // and a term for products below the smallest float32 (`tiny`). (Denormal
 // bf16 inputs and float32 results are kept by this instruction: checked on
 // an MI355X, where the largest error found over adversarial operands was
-// 2.5 * 2^-23 * a for an instruction's 32 products.) A bound that is not
+// 3.8 * 2^-23 * a for an instruction's 32 products and 8.2 * 2^-23 * a for an
+// accumulator's 256.) A bound that is not
 // finite keeps its expert.
 //
 // Selection: tau, the k-th largest of the 64 lanes' largest s~ - B (lane l

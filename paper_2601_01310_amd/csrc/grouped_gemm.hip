@@ -49,11 +49,12 @@
 // batch, a replay, a small model, some tens of rows per slot). Results of the
 // ring shapes are staged through each wave's own LDS region and written as
 // 16-byte row segments. All shapes give identical bits, so the choice never
-// changes a result. Measured, us, gate/up + down, before (the first two shapes
-// only) -> now: one DeepSeek-V3 expert (d 7168, I 2048) of 48 rows 84 + 17 ->
-// 24 + 13, of 1024 rows 145 + 46 -> 73 + 38; one Mixtral expert (d 4096,
-// I 14336) of one row 61 + 77 -> 52 + 36, of 333 rows 95 + 119 -> 95 + 81;
-// four DeepSeek-V3 experts of 32 rows 92 + 32 -> 43 + 32.
+// changes a result. Measured, us, both projections, weights from HBM (repeated
+// on one copy, of which up to 256 MB stay in the Infinity Cache), before (the
+// first two shapes only) -> now: one DeepSeek-V3 expert (d 7168, I 2048) of 48
+// rows 96 -> 34 (58 -> 31), of 1024 rows 177 -> 117 (165 -> 107); one Mixtral
+// expert (d 4096, I 14336) of one row 130 -> 80 (128 -> 76), of 333 rows
+// 215 -> 177 (214 -> 175); four DeepSeek-V3 experts of 32 rows 121 -> 74.
 //
 // Tile order: the tiles of one launch are enumerated slot by slot, then by
 // weight panel (n), then by row block (m), so consecutive tiles share a
