@@ -565,19 +565,20 @@ hipError_t remap_dispatch(bool replay, const int32_t* ids, int T, int k, const i
   const int sbits = (S > 1) ? 32 - __builtin_clz((unsigned)(S - 1)) : 0;
   if (npairs <= kSmallPairs) {
     if (replay)
-      hipLaunchKernelGGL(dispatch_one_block_kernel<true>, dim3(sched ? 2 : 1), dim3(kOneBlock), 0, stream, ids,
-                         npairs, k, ert, E, R, alive, S, sbits, nullptr, prior, pair_slot, counts,
-                         offsets, perm, pair_row, n_unserved, total_out, sched, dims);
+      hipLaunchKernelGGL(dispatch_one_block_kernel<true>, dim3(sched ? 2 : 1), dim3(kOneBlock), 0,
+                         stream, ids, npairs, k, ert, E, R, alive, S, sbits, nullptr, prior,
+                         pair_slot, counts, offsets, perm, pair_row, n_unserved, total_out, sched,
+                         dims);
     else
-      hipLaunchKernelGGL(dispatch_one_block_kernel<false>, dim3(sched ? 2 : 1), dim3(kOneBlock), 0, stream,
-                         ids, npairs, k, ert, E, R, alive, S, sbits, token_valid, nullptr,
+      hipLaunchKernelGGL(dispatch_one_block_kernel<false>, dim3(sched ? 2 : 1), dim3(kOneBlock), 0,
+                         stream, ids, npairs, k, ert, E, R, alive, S, sbits, token_valid, nullptr,
                          pair_slot, counts, offsets, perm, pair_row, n_unserved, total_out, sched,
                          dims);
   } else {
     if (replay)
-      hipLaunchKernelGGL(remap_count_kernel<true>, dim3(nchunks), dim3(kBlock), 0, stream, ids, npairs,
-                         k, ert, E, R, alive, S, nullptr, prior, pair_slot, hist, unserved_chunk,
-                         chunk, sched);
+      hipLaunchKernelGGL(remap_count_kernel<true>, dim3(nchunks), dim3(kBlock), 0, stream, ids,
+                         npairs, k, ert, E, R, alive, S, nullptr, prior, pair_slot, hist,
+                         unserved_chunk, chunk, sched);
     else
       hipLaunchKernelGGL(remap_count_kernel<false>, dim3(nchunks), dim3(kBlock), 0, stream, ids,
                          npairs, k, ert, E, R, alive, S, token_valid, nullptr, pair_slot, hist,

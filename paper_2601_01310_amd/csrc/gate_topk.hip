@@ -754,12 +754,13 @@ __global__ __launch_bounds__(256) void logits_topk_rounds_kernel(const float* __
 // candidates alternate between two halves, which are even for any E: with the
 // lower and the upper half of NQ, 16384 tokens of 160 experts, k = 8, took 8.4 us
 // instead of 6.2), or lower where some are equal, is reached by at least k
-// candidates, so only candidates >= tau can be chosen: k and a few more. They are gathered into the row's lanes through LDS, a lane's rank is
-// the number of larger keys among the row's 16, and the lanes take their
-// candidates in rank order. With more than 16 candidates in one of the wave's
-// rows (k near 16, many equal logits, or NaN among them) the wave finds the
-// winners round by round after all, having formed tau for nothing: 10 to 30 %
-// slower than the other kernel.
+// candidates, so only candidates >= tau can be chosen: k and a few more. They
+// are gathered into the row's lanes through LDS, a lane's rank is the number of
+// larger keys among the row's 16, and the lanes take their candidates in rank
+// order. With more than 16 candidates in one of the wave's rows (k near 16,
+// many equal logits, or NaN among them) the wave finds the winners round by
+// round after all, having formed tau for nothing: 10 to 30 % slower than the
+// other kernel.
 template <int NQ>
 __global__ __launch_bounds__(256) void logits_topk_rows_kernel(const float* __restrict__ logits,
                                                                int T, int E, int k,
